@@ -20,9 +20,9 @@
 //   k_rows   -- one wave per row builds rows in registers from the lists
 //               (canonical rows of handles without a dense table).
 // Serving (Section 2, Eq. 1 and the extended transition function):
-//   k_apply  -- write-mostly masking of [B, V] logits (lists, tail rows, and
-//               unaligned rows); k_apply_dense for dense-table rows, three
-//               rows per block (two for small batches).
+//   k_apply  -- write-mostly masking of [B, V] logits (lists and tail rows);
+//               k_apply_dense for dense-table rows, three rows per block (two
+//               for small batches); rows of any alignment.
 //   k_advance-- B byte walks over the child tables and along the strings of
 //               the blob, one wave per row.
 //   k_export_dense, k_export_tail -- canonical rows out of the dense table and
@@ -55,9 +55,9 @@ constexpr int kWave = 64;
 constexpr int kApplyUnits = 1;       // 16-byte chunks per thread in k_apply (measured best)
 constexpr int kApplyRows = 3;        // rows per block of k_apply_dense (measured best on rows that change every call)
 constexpr int64_t kApplyMinBlocks = 4096;  // fewer blocks than this with kApplyRows: two rows per block
-// k_apply row sources: the dense table, the valid lists, or per row either
-// (tail compression: dense rows for branching nodes, lists for tails)
-constexpr int kApplyTable = 0, kApplyLists = 1, kApplyTail = 2;
+// k_apply row sources: the valid lists, or with tail compression per row the
+// tail's hits or the branching node's dense row or list
+constexpr int kApplyLists = 1, kApplyTail = 2;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -811,6 +811,22 @@ struct NegInf<uint32_t> {
     static constexpr uint32_t bits = 0xFF800000u;
 };
 
+// The E mask bits of chunk c of a row shifted by a elements (see row_shift),
+// from dense table row trow: the bits of the tokens c E - a .. c E - a + E - 1,
+// 0 for tokens below 0 (bits of tokens >= V are 0 in the table, and bytes past
+// the row are not read).
+template <int E>
+__device__ __forceinline__ uint32_t table_bits(const DevTables &t, int64_t trow, int64_t c, int a) {
+    const uint8_t *mrow = reinterpret_cast<const uint8_t *>(t.table + trow * t.Wp);
+    constexpr uint32_t FULL = (1u << E) - 1u;
+    const int64_t i0 = c * E - a;
+    if (a == 0) return E == 8 ? (uint32_t)mrow[c] : ((uint32_t)mrow[c >> 1] >> ((c & 1) * 4)) & FULL;
+    const int64_t k0 = i0 >> 3, k1 = (i0 + E - 1) >> 3;  // one byte or two neighbours
+    const uint32_t x0 = k0 >= 0 ? mrow[k0] : 0u;
+    const uint32_t x1 = k1 != k0 && k1 < t.Wp * 8 ? mrow[k1] : 0u;
+    return ((x0 | (x1 << 8)) >> (i0 & 7)) & FULL;
+}
+
 // One token id per lane (rel = id minus the first element of the block's span;
 // >= kSpan: none or outside): each thread sets the bits of its own chunks.  The
 // ids inside the span are few, so a ballot keeps only those.
@@ -838,34 +854,66 @@ __device__ __forceinline__ void set_id(uint32_t rel, uint32_t (&bits)[kApplyUnit
         if (lc == (uint32_t)(u * kBlock + threadIdx.x)) bits[u] |= 1u << (rel % E);
 }
 
-// Grid: x = groups of kBlock*kApplyUnits chunks of one row, y = batch row.
-// A chunk is 16 bytes of logits (8 bf16 or 4 fp32); thread i of a block owns
-// chunks c0 + u*kBlock + i, so every store instruction covers 4 KiB per block
-// contiguously (one chunk per thread writes fastest, as for the table's zero
-// fill).  All mask bits of the thread are read before its first store.
+// A chunk is 16 bytes of logits memory (E = 8 bf16 or 4 fp32 elements).  A row
+// whose base is `a` elements past a 16-byte boundary (a = 0 when the logits and
+// their row stride are 16-byte aligned; an odd vocabulary with contiguous rows
+// gives every a) has its chunks shifted by a: chunk c holds the elements c E - a
+// .. c E - a + E - 1, and only the row's first and last chunk may be partial.
+// So every row, aligned or not, is written in whole 16-byte stores; going
+// element by element instead, a decode step (apply + advance) of 64 unaligned
+// fp32 rows over V = 128,255 took 23.7 us against 12.9 us this way.
+template <typename T>
+__device__ __forceinline__ int row_shift(const T *row) {
+    return (int)((reinterpret_cast<uintptr_t>(row) & 15) / sizeof(T));
+}
+
+// -inf into the elements of a partial chunk [e0, e0 + E) inside [0, V) whose
+// bit in bu is 0.  kAligned: e0 >= 0, only the row's end can cut a chunk.
+template <typename T, bool kAligned>
+__device__ __forceinline__ void mask_partial(T *row, int64_t e0, int64_t V, uint32_t bu) {
+    constexpr int E = 16 / (int)sizeof(T);
+    const int lim = (int)min<int64_t>(E, V - e0);
+    for (int i = kAligned || e0 >= 0 ? 0 : (int)-e0; i < lim; ++i)
+        if (!((bu >> i) & 1u)) row[e0 + i] = NegInf<T>::bits;
+}
+
+// Chunk [e0, e0 + E) lies inside the row.
+template <bool kAligned, int E>
+__device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
+    return (kAligned || e0 >= 0) && e0 + E <= V;
+}
+
+// List and tail rows.  Grid: x = groups of kBlock*kApplyUnits chunks of one row,
+// y = batch row.
+// Thread i of a block owns chunks c0 + u*kBlock + i, so every store instruction
+// covers 4 KiB per block contiguously (one chunk per thread writes fastest, as
+// for the table's zero fill).  All mask bits of the thread are read before its
+// first store.
 // Write-mostly: a chunk without a valid token gets one non-temporal -inf store
-// and no read; a fully valid chunk is skipped; a mixed chunk is read, merged and
-// written (dense table), or gets -inf stores into its invalid elements only
-// (lists).  List rows (kApplyLists, and the tail rows of kApplyTail): the bits
-// of the block's span come from the node's valid list instead of the dense
-// table (a ballot over a short list, an LDS bitmap for a long one).
-// vec == 0: rows are not 16-byte aligned; go element by element.
-template <typename T, int kMode>
+// and no read; a fully valid chunk is skipped; a mixed chunk gets -inf stores
+// into its invalid elements only.  The bits of the block's span come from the
+// node's valid list (a ballot over a short list, an LDS bitmap for a long one),
+// from the tail's hits, or (kApplyTail) from the dense row of a branching node.
+// kAligned: every row's base is 16-byte aligned (no shift; computing it all the
+// same costs 1-2% of a forest's or a code list's decode step, as does unrolling
+// mask_partial).
+template <typename T, int kMode, bool kAligned>
 __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__restrict__ node_ids,
-                                                  T *__restrict__ logits, int64_t stride, int vec) {
+                                                  T *__restrict__ logits, int64_t stride) {
     constexpr int E = 16 / (int)sizeof(T);
     constexpr uint32_t FULL = (1u << E) - 1u;
     constexpr T NEG = NegInf<T>::bits;
     constexpr int kSpan = kBlock * kApplyUnits * E;  // elements per block
-    __shared__ uint32_t bm[kMode != kApplyTable ? kSpan / 32 : 1];
+    __shared__ uint32_t bm[kSpan / 32];
 
     const int64_t V = t.V;
     const int64_t b = blockIdx.y;
     const int32_t n = node_ids[b];
     const bool live = n >= 0 && (int64_t)n < t.N;
     const int64_t c0 = (int64_t)blockIdx.x * kBlock * kApplyUnits;
-    const int64_t nchunks = (V + E - 1) / E;
     T *row = logits + b * stride;
+    const int a = kAligned ? 0 : row_shift(row);
+    const int64_t nchunks = (V + a + E - 1) / E;
     // the row's source (uniform over the block): its dense table row, its list,
     // or (a tail with tail compression) the probe's hits along its path
     const int lane = threadIdx.x & (kWave - 1);
@@ -884,7 +932,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
     uint32_t bits[kApplyUnits];
 #pragma unroll
     for (int u = 0; u < kApplyUnits; ++u) bits[u] = 0;
-    const uint32_t lo = (uint32_t)(c0 * E);
+    const uint32_t lo = (uint32_t)(c0 * E - a);  // first element of the span (wraps below 0 in the first one)
     if (tail_row) {
         // lane d-1 takes the token of length d starting below the tail (the
         // path below a tail has consecutive ids, so all of them were loaded)
@@ -932,15 +980,11 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
                 bits[u] = (bm[bit >> 5] >> (bit & 31)) & FULL;
             }
         }
-    } else {
-        const uint8_t *mrow = reinterpret_cast<const uint8_t *>(t.table + (trow >= 0 ? trow * t.Wp : 0));
+    } else if (trow >= 0) {
 #pragma unroll
         for (int u = 0; u < kApplyUnits; ++u) {
             const int64_t c = c0 + u * kBlock + threadIdx.x;
-            uint32_t x = 0;
-            if (trow >= 0 && c < nchunks)
-                x = E == 8 ? (uint32_t)mrow[c] : ((uint32_t)mrow[c >> 1] >> ((c & 1) * 4)) & FULL;
-            bits[u] = x;
+            if (c < nchunks) bits[u] = table_bits<E>(t, trow, c, a);
         }
     }
 
@@ -950,8 +994,8 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
         if (c >= nchunks) break;
         const uint32_t bu = bits[u];
         if (bu == FULL) continue;
-        const int64_t e0 = c * E;
-        if (vec && e0 + E <= V) {
+        const int64_t e0 = c * E - a;
+        if (whole_chunk<kAligned, E>(e0, V)) {
             u32x4 *p = reinterpret_cast<u32x4 *>(row + e0);
             if (bu == 0) {
                 const uint32_t w = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
@@ -988,9 +1032,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
                 *p = x;
             }
         } else {
-            const int lim = (int)min<int64_t>(E, V - e0);
-            for (int i = 0; i < lim; ++i)
-                if (!((bu >> i) & 1u)) row[e0 + i] = NEG;
+            mask_partial<T, kAligned>(row, e0, V, bu);
         }
     }
 }
@@ -1001,45 +1043,42 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
 // stores: a block keeps kApplyRows mask loads in flight, while at any moment
 // the blocks still write a few compact windows of the logits.  Write-mostly as
 // in k_apply (non-temporal -inf stores, read-merge-write of mixed chunks, also
-// stored non-temporally).
-template <typename T, int R>
+// stored non-temporally).  kAligned: every row's base is 16-byte aligned, so the
+// rows' chunks share their elements and no shift is computed.
+template <typename T, int R, bool kAligned>
 __global__ void __launch_bounds__(kBlock) k_apply_dense(DevTables t, const int32_t *__restrict__ node_ids,
                                                         int64_t rows, T *__restrict__ logits, int64_t stride) {
     constexpr int E = 16 / (int)sizeof(T);
     constexpr uint32_t FULL = (1u << E) - 1u;
     constexpr T NEG = NegInf<T>::bits;
-    const int64_t V = t.V, nchunks = (V + E - 1) / E;
+    const int64_t V = t.V;
     const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t e0 = c * E;
-    const uint8_t *table = reinterpret_cast<const uint8_t *>(t.table);
-    const int64_t row_bytes = t.Wp * 8;
+    int a[R];
+    bool in[R];  // the row exists and has a chunk c
     uint32_t bits[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t b = (int64_t)blockIdx.y * R + r;
+        a[r] = kAligned ? 0 : row_shift(logits + b * stride);
+        in[r] = b < rows && c < (V + a[r] + E - 1) / E;
         const int32_t n = b < rows ? node_ids[b] : -1;
         bits[r] = 0;  // a dead row: every token invalid
-        if (n >= 0 && (int64_t)n < t.N && c < nchunks) {
-            const uint8_t *mrow = table + (int64_t)n * row_bytes;
-            bits[r] = E == 8 ? (uint32_t)mrow[c] : ((uint32_t)mrow[c >> 1] >> ((c & 1) * 4)) & FULL;
-        }
+        if (n >= 0 && (int64_t)n < t.N && in[r]) bits[r] = table_bits<E>(t, n, c, a[r]);
     }
-    if (c >= nchunks) return;
-    const bool whole = e0 + E <= V;
     u32x4 xv[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int64_t b = (int64_t)blockIdx.y * R + r;
-        if (b < rows && whole && bits[r] != 0 && bits[r] != FULL)
+        const int64_t b = (int64_t)blockIdx.y * R + r, e0 = c * E - a[r];
+        if (in[r] && whole_chunk<kAligned, E>(e0, V) && bits[r] != 0 && bits[r] != FULL)
             xv[r] = *reinterpret_cast<const u32x4 *>(logits + b * stride + e0);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int64_t b = (int64_t)blockIdx.y * R + r;
+        const int64_t b = (int64_t)blockIdx.y * R + r, e0 = c * E - a[r];
         const uint32_t bu = bits[r];
-        if (b >= rows || bu == FULL) continue;
+        if (!in[r] || bu == FULL) continue;
         T *row = logits + b * stride;
-        if (whole) {
+        if (whole_chunk<kAligned, E>(e0, V)) {
             u32x4 *p = reinterpret_cast<u32x4 *>(row + e0);
             if (bu == 0) {
                 const uint32_t w = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
@@ -1055,9 +1094,7 @@ __global__ void __launch_bounds__(kBlock) k_apply_dense(DevTables t, const int32
                 __builtin_nontemporal_store(o, p);
             }
         } else {
-            const int lim = (int)min<int64_t>(E, V - e0);
-            for (int i = 0; i < lim; ++i)
-                if (!((bu >> i) & 1u)) row[e0 + i] = NEG;
+            mask_partial<T, kAligned>(row, e0, V, bu);
         }
     }
 }
@@ -2016,18 +2053,37 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
 
 // Dense-table rows, R rows per block; grid.y (row groups) is limited to 65535
 // per launch.
-template <int R>
+template <int R, bool kAligned>
 static hipError_t launch_apply_dense(const DevTables &t, const int32_t *node_ids, int64_t B, void *logits, int dtype,
                                      int64_t row_stride, int64_t gx1, hipStream_t s) {
     for (int64_t r0 = 0; r0 < B; r0 += (int64_t)65535 * R) {
         const int64_t rows = std::min<int64_t>(B - r0, (int64_t)65535 * R);
         const dim3 grid((unsigned)gx1, (unsigned)grid_for(rows, R));
         if (dtype == TAM_DTYPE_BF16)
-            hipLaunchKernelGGL((k_apply_dense<uint16_t, R>), grid, dim3(kBlock), 0, s, t, node_ids + r0, rows,
+            hipLaunchKernelGGL((k_apply_dense<uint16_t, R, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, rows,
                                static_cast<uint16_t *>(logits) + r0 * row_stride, row_stride);
         else
-            hipLaunchKernelGGL((k_apply_dense<uint32_t, R>), grid, dim3(kBlock), 0, s, t, node_ids + r0, rows,
+            hipLaunchKernelGGL((k_apply_dense<uint32_t, R, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, rows,
                                static_cast<uint32_t *>(logits) + r0 * row_stride, row_stride);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// List and tail rows; grid.y is limited to 65535 rows per launch.
+template <typename T, bool kAligned>
+static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, void *logits,
+                                    int64_t row_stride, unsigned gx, hipStream_t s) {
+    for (int64_t r0 = 0; r0 < B; r0 += 65535) {
+        const dim3 grid(gx, (unsigned)std::min<int64_t>(B - r0, 65535));
+        T *p = static_cast<T *>(logits) + r0 * row_stride;
+        if (t.row_of)
+            hipLaunchKernelGGL((k_apply<T, kApplyTail, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
+                               row_stride);
+        else
+            hipLaunchKernelGGL((k_apply<T, kApplyLists, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
+                               row_stride);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -2038,45 +2094,25 @@ hipError_t launch_apply(const DevTables &t, const int32_t *node_ids, int64_t B, 
                         int64_t row_stride, hipStream_t s) {
     const int E = dtype == TAM_DTYPE_BF16 ? 8 : 4;
     const int elem = dtype == TAM_DTYPE_BF16 ? 2 : 4;
-    const int64_t nchunks = (t.V + E - 1) / E;
-    const unsigned gx = grid_for(nchunks, kBlock * kApplyUnits);
-    const int vec = ((reinterpret_cast<uintptr_t>(logits) & 15) == 0 && ((row_stride * elem) & 15) == 0)
-                        ? 1
-                        : 0;
-    const int mode = t.row_of ? kApplyTail : (t.table ? kApplyTable : kApplyLists);
-    if (mode == kApplyTable && vec) {
+    const bool aligned = (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && ((row_stride * elem) & 15) == 0;
+    const int64_t nchunks = (t.V + (aligned ? 0 : E - 1) + E - 1) / E;  // a shifted row may touch one more
+    if (!t.row_of && t.table) {
         const int64_t gx1 = grid_for(nchunks, kBlock);
         // three rows per block while that keeps 16 blocks per CU in flight,
         // else two (64 fp32 rows over V = 128,256: 8.2 against 8.9 µs per call)
-        if (gx1 * ((B + kApplyRows - 1) / kApplyRows) >= kApplyMinBlocks)
-            return launch_apply_dense<kApplyRows>(t, node_ids, B, logits, dtype, row_stride, gx1, s);
-        return launch_apply_dense<2>(t, node_ids, B, logits, dtype, row_stride, gx1, s);
+        const bool three = gx1 * ((B + kApplyRows - 1) / kApplyRows) >= kApplyMinBlocks;
+        if (aligned)
+            return three ? launch_apply_dense<kApplyRows, true>(t, node_ids, B, logits, dtype, row_stride, gx1, s)
+                         : launch_apply_dense<2, true>(t, node_ids, B, logits, dtype, row_stride, gx1, s);
+        return three ? launch_apply_dense<kApplyRows, false>(t, node_ids, B, logits, dtype, row_stride, gx1, s)
+                     : launch_apply_dense<2, false>(t, node_ids, B, logits, dtype, row_stride, gx1, s);
     }
-    // grid.y is limited to 65535 rows per launch
-    for (int64_t r0 = 0; r0 < B; r0 += 65535) {
-        const dim3 grid(gx, (unsigned)std::min<int64_t>(B - r0, 65535));
-        const int32_t *ids = node_ids + r0;
-        if (dtype == TAM_DTYPE_BF16) {
-            uint16_t *p = static_cast<uint16_t *>(logits) + r0 * row_stride;
-            if (mode == kApplyLists)
-                hipLaunchKernelGGL((k_apply<uint16_t, kApplyLists>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride, vec);
-            else if (mode == kApplyTail)
-                hipLaunchKernelGGL((k_apply<uint16_t, kApplyTail>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride, vec);
-            else
-                hipLaunchKernelGGL((k_apply<uint16_t, kApplyTable>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride, vec);
-        } else {
-            uint32_t *p = static_cast<uint32_t *>(logits) + r0 * row_stride;
-            if (mode == kApplyLists)
-                hipLaunchKernelGGL((k_apply<uint32_t, kApplyLists>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride, vec);
-            else if (mode == kApplyTail)
-                hipLaunchKernelGGL((k_apply<uint32_t, kApplyTail>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride, vec);
-            else
-                hipLaunchKernelGGL((k_apply<uint32_t, kApplyTable>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride, vec);
-        }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const unsigned gx = grid_for(nchunks, kBlock * kApplyUnits);
+    if (dtype == TAM_DTYPE_BF16)
+        return aligned ? launch_apply_rows<uint16_t, true>(t, node_ids, B, logits, row_stride, gx, s)
+                       : launch_apply_rows<uint16_t, false>(t, node_ids, B, logits, row_stride, gx, s);
+    return aligned ? launch_apply_rows<uint32_t, true>(t, node_ids, B, logits, row_stride, gx, s)
+                   : launch_apply_rows<uint32_t, false>(t, node_ids, B, logits, row_stride, gx, s);
 }
 
 hipError_t launch_advance(const DevTables &t, const int32_t *node_ids, const int32_t *token_ids, int64_t B,

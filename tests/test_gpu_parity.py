@@ -994,6 +994,34 @@ def test_ragged_vocab_and_strides(P, flags):
     assert h.advance(empty, empty).numel() == 0
 
 
+@pytest.mark.parametrize("flags", FLAGS, ids=FLAG_IDS)
+@pytest.mark.parametrize("V", [1, 7, 8, 9, 63, 64, 65, 1023, 1024, 1025, 2047, 2048, 2049, 4099])
+def test_apply_rows_at_every_alignment(P, flags, V):
+    """Rows whose base lies 0 .. E - 1 elements past a 16-byte boundary, at the
+    edges of a 16-byte chunk, a mask word and a block's span; what lies between
+    the rows is not touched."""
+    w = W.config(1)
+    vocab = (w.vocab[97:123] + w.vocab[:97] + w.vocab[123:])[:V]  # the letters first
+    o = Oracle(w.strings, vocab)
+    h = P.compile(w.strings, vocab, flags=flags)
+    nodes = np.array([0, 1, 5, o.N // 2, o.N - 1, -1, 0, 1, 0], dtype=np.int32)
+    ids = torch.as_tensor(nodes, device="cuda")
+    B = len(nodes)
+    for dtype in ("fp32", "bf16"):
+        E, np_t = (8, np.uint16) if dtype == "bf16" else (4, np.uint32)
+        for off in range(E):
+            for pad in (0, 1, E - off % E):
+                stride = V + pad
+                x = host_logits(1, off + B * stride + E, dtype, seed=off)
+                dev = x.cuda()
+                rows = dev[0, off:off + B * stride].view(B, stride)[:, :V]
+                h.apply_mask(ids, rows)
+                exp = bits_of(x).view(np_t).copy()
+                inner = exp[0, off:off + B * stride].reshape(B, stride)
+                inner[:, :V] = o.apply(nodes, np.ascontiguousarray(inner[:, :V]), 1 if dtype == "bf16" else 0)
+                assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, off, pad)
+
+
 def test_many_rows_grid_split(P):
     """More than 65,535 batch rows in one call (the launcher splits the grid)."""
     strings = [b"ab", b"b"]
