@@ -1255,36 +1255,94 @@ __device__ __forceinline__ bool format_fits(const DevTables &t, int p, const uin
     return true;
 }
 
+// The positions q = 64 k .. 64 k + 63 whose class admits byte c (position L: the
+// terminator alone; past it none), bit q - 64 k each.
+__device__ __forceinline__ uint64_t class_word(const DevTables &t, int64_t k, uint32_t c) {
+    uint64_t x = 0;
+    const int64_t q0 = 64 * k;
+    const int n = (int)min<int64_t>(64, (int64_t)t.fmt_L - q0);
+#pragma unroll 4
+    for (int j = 0; j < n; ++j)
+        x |= (uint64_t)((t.classes[(q0 + j) * 32 + (c >> 3)] >> (c & 7)) & 1u) << j;
+    const int64_t e = (int64_t)t.fmt_L - q0;  // the terminator's position
+    if (e >= 0 && e < 64 && c == (uint32_t)t.terminator) x |= 1ull << e;
+    return x;
+}
+
 // Character-position masks (Appendix, Constraint-Aware Dispatch Beyond Finite
-// Sets), written whole: one wave per 64-token word w of every row.  Lane i
-// tests token 64 w + i at each position p; the wave's ballot is word w of row p
-// (lane 0 stores it at out[p * stride + w]), so no zero fill is needed, and
-// words past V come out zero.  The valid (position, token) pairs are counted:
-// per block into pairs[blockIdx.x], and/or added to *total.
+// Sets), written whole: one wave per 64-token word w of every row, 64 positions
+// at a time.  LDS holds for every byte the set of positions whose class admits
+// it, so lane i finds all positions of a window where token 64 w + i fits with one
+// AND per token byte (that set shifted down by the byte's index); the wave's
+// ballot over bit j is word w of the window's row j, kept by lane j and stored at
+// out[row * stride + w], so no zero fill is needed, and words past V come out
+// zero.  Testing every position byte by byte instead was bound by those serial
+// checks: a 36-character format over V = 262,144 took 41.5 us, this way 8.7 us.
+// The valid (position, token) pairs are counted: per block into
+// pairs[blockIdx.x], and/or added to *total.
 __global__ void __launch_bounds__(kBlock) k_format(DevTables t, uint64_t *__restrict__ out, int64_t stride,
                                                    int64_t nwords, int32_t *__restrict__ pairs,
                                                    unsigned long long *total) {
+    __shared__ uint64_t cls[2][256];  // the window's class words, and the next window's
+    static_assert(kBlock == 256, "one thread per byte value");
     const int64_t w = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t v = w * kWave + lane;
     int32_t found = 0;
-    if (w < nwords) {
-        int len = 0;
-        const uint8_t *tb = t.tok_blob;
-        if (v < t.V) {
-            const uint32_t o = t.tok_off[v];
-            len = (int)(t.tok_off[v + 1] - o);
-            tb += o;
+    int len = 0;
+    uint32_t o = 0;
+    if (w < nwords && v < t.V) {
+        o = t.tok_off[v];
+        len = (int)(t.tok_off[v + 1] - o);
+    }
+    // the token's bytes from i on, eight at a time (three aligned dwords; the
+    // token blob is padded)
+    auto bytes8 = [&](int i) {
+        const uint32_t at = o + (uint32_t)i;
+        const uint32_t *q = reinterpret_cast<const uint32_t *>(t.tok_blob + (at & ~3u));
+        const uint32_t sh = (at & 3u) * 8u;
+        const uint32_t q0 = q[0], q1 = q[1], q2 = q[2];
+        return (uint64_t)(uint32_t)((((uint64_t)q1 << 32) | q0) >> sh) |
+               ((uint64_t)(uint32_t)((((uint64_t)q2 << 32) | q1) >> sh) << 32);
+    };
+    const uint64_t head = len > 0 ? bytes8(0) : 0;
+    const int64_t rows = (int64_t)t.fmt_L + 2, nwin = (rows + 63) / 64;
+    cls[1][threadIdx.x] = class_word(t, 0, threadIdx.x);
+    for (int64_t k = 0; k < nwin; ++k) {
+        const uint64_t here = cls[1][threadIdx.x];
+        const uint64_t next = k + 1 < nwin ? class_word(t, k + 1, threadIdx.x) : 0;
+        __syncthreads();  // the last window's reads are done
+        cls[0][threadIdx.x] = here;
+        cls[1][threadIdx.x] = next;
+        __syncthreads();
+        if (w >= nwords) continue;  // uniform over the wave
+        uint64_t m = len > 0 ? ~0ull : 0;  // bit j: the token fits at position 64 k + j so far
+        if (len <= 64) {
+            uint64_t x = head;
+            for (int i = 0; __any(i < len && m != 0); ++i) {
+                if (i >= len || m == 0) continue;
+                if (i > 0 && (i & 7) == 0) x = bytes8(i);
+                const uint32_t c = (uint32_t)(x >> (8 * (i & 7))) & 0xffu;
+                m &= (cls[0][c] >> i) | (i ? cls[1][c] << (64 - i) : 0);
+            }
+        } else {  // a token longer than a window (rare): position by position
+            m = 0;
+            for (int j = 0; j < 64; ++j)
+                if (64 * k + j < rows && format_fits(t, (int)(64 * k + j), t.tok_blob + o, len)) m |= 1ull << j;
         }
-        for (int p = 0; p <= t.fmt_L + 1; ++p) {
-            const bool ok = format_fits(t, p, tb, len);
-            const uint64_t word = __ballot(ok);
-            if (lane == 0) out[(int64_t)p * stride + w] = word;
-            found += ok ? 1 : 0;
+        found += __popcll(m);
+        const int n = (int)min<int64_t>(64, rows - 64 * k);
+        uint64_t mine = 0;
+        if (__any(m != 0)) {
+            for (int j = 0; j < n; ++j) {
+                const uint64_t word = __ballot((m >> j) & 1u);
+                if (lane == j) mine = word;
+            }
         }
+        if (lane < n) out[(64 * k + lane) * stride + w] = mine;
     }
     __shared__ int32_t wsum[kBlock / kWave];
-    for (int o = kWave / 2; o > 0; o >>= 1) found += __shfl_xor(found, o, kWave);
+    for (int o2 = kWave / 2; o2 > 0; o2 >>= 1) found += __shfl_xor(found, o2, kWave);
     if (lane == 0) wsum[threadIdx.x / kWave] = found;
     __syncthreads();
     if (threadIdx.x == 0) {

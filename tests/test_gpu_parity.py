@@ -946,6 +946,28 @@ def test_format_masks(P, c4_vocab, name):
     h.close()
 
 
+@pytest.mark.parametrize("L", [1, 61, 62, 63, 64, 65, 126, 127, 128, 191])
+def test_format_window_edges(P, L):
+    """Formats whose positions end at the edges of a 64-position window, with
+    tokens up to and beyond a window's length; V ends inside a word."""
+    from oracle import Format
+    rng = np.random.default_rng(L)
+    classes = [bytes(rng.choice(np.frombuffer(b"abc", np.uint8), size=rng.integers(2, 4), replace=False)) for _ in range(L)]
+    vocab = [bytes([c]) for c in range(256)] + [b""]
+    for n in list(range(2, 20)) + [31, 32, 33, 62, 63, 64, 65, 66, 100, 127, 128, 129]:
+        for _ in range(6):
+            at = int(rng.integers(0, max(1, L + 2 - n)))  # cut from a value that fits at `at`
+            t = [c[int(rng.integers(0, len(c)))] for c in (classes + [b'"'])[at:at + n]]
+            vocab.append(bytes(t) if len(t) == n else bytes(rng.choice(np.frombuffer(b'abc"', np.uint8), size=n)))
+    f = Format(classes, vocab)
+    h = P.compile_format(classes, vocab)
+    pos = np.arange(-1, L + 3, dtype=np.int32)
+    rows = f.mask_rows(pos)
+    assert np.array_equal(gpu_rows(h, pos), rows)
+    assert h.valid_pairs() == int(np.unpackbits(rows.view(np.uint8)).sum())
+    h.close()
+
+
 def test_format_decode_reaches_final(P, c4_vocab):
     """Decoding a date with uniformly random valid tokens always ends at the
     final position, having written L characters and the terminator."""
