@@ -92,9 +92,30 @@ struct StrRec {
 // prefix in its part) are branching and take dense rows row, row + 1, ... in
 // order; the others are tails, with len - i nodes below them and
 // tail_span = i - top (top: the path index above the string's highest tail,
-// -1 when the set's root is itself a tail).
+// -1 when the set's root is itself a tail).  root: row_of of the set's root.
 struct TailRec {
-    int32_t row, next, top;
+    int32_t row, next, top, root;
+};
+
+// What a walk reads per node.  The nodes a string creates have consecutive ids,
+// so a node's own path goes on at the next id; only its other children (each the
+// first node of a later string that branches off there) are listed: n entries
+// from `off` on, in no fixed order.
+struct alignas(8) Walk {
+    int32_t off;
+    uint32_t nb;  // the node's edge byte (a root: any but the terminator) | n << 8
+};
+struct alignas(16) Kid {
+    int32_t node, off;  // the child, and its Walk: its own other children
+    uint32_t nb;        // and edge byte
+    int32_t unused;
+};
+
+// The first bytes of a token, for walks: byte 15 is its length, or 255 for a
+// token longer than kHeadLen bytes (then read from tok_blob).
+constexpr int kHeadLen = 15;
+struct alignas(16) TokHead {
+    uint8_t b[16];
 };
 
 // ---------------------------------------------------------------------------
@@ -120,14 +141,12 @@ struct DevTables {
     const int32_t *node_at;     // [blob_bytes] node whose edge byte is that blob byte (pad: root)
     const int32_t *node_pos;    // [N] blob offset of the node's edge byte (-1 at roots)
     const int32_t *depth;       // [N]
-    const int32_t *child_off;   // [N+1]
-    const uint8_t *child_byte;  // [N-S]
-    const int32_t *child_node;  // [N-S]
-    const int32_t *child_pos;   // [N-S] node_pos of child_node[k]: where a walk goes on along its string
-    const uint64_t *child_at;   // [blob_bytes] child range of node_at[p]: child_off lo | hi << 32
+    const Walk *walk;           // [N] edge byte and other children
+    const Kid *kid;             // [at most K] the other children's entries
     // vocabulary (a2)
     const uint32_t *tok_off;    // [V+1]
     const uint8_t *tok_blob;
+    const TokHead *tok_head;    // [V]
     const uint16_t *fps;        // [slot_mask+1] fingerprints, kBucket per bucket
     const SlotPay *pay;         // [slot_mask+1]
     const uint64_t *pay_hi;     // [slot_mask+1] bytes 8..15 of the reversed token

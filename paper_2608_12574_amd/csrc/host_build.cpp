@@ -125,6 +125,7 @@ struct PartBase {
     int64_t node;         // local node i >= 1 gets id node + i
     int64_t blob;         // local blob offset b goes to blob + b
     bool root_tail;       // its set has one string (the set root is then a tail)
+    int32_t root_row;     // (tail split) row_of of its set's root
     int64_t str0;         // blob-order index of its first string
     int64_t first_row;    // (tail split) dense row of the part's first branching node
 };
@@ -176,7 +177,7 @@ void emit_part(const uint8_t *sb, const int64_t *so, uint8_t term, const PartPla
         h->strs[(size_t)(pb.str0 + u)] = StrRec{(int32_t)at, (int32_t)len, (int32_t)l, (int32_t)(pb.node + N),
                                                 psv < 0 ? -1 : (int32_t)(pb.str0 + psv), pb.root};
         h->blob[(size_t)at] = 0;
-        if (tails) h->tail_rec[(size_t)(pb.str0 + u)] = TailRec{row, (int32_t)next, (int32_t)top};
+        if (tails) h->tail_rec[(size_t)(pb.str0 + u)] = TailRec{row, (int32_t)next, (int32_t)top, pb.root_row};
         if (host_tables) h->row_at[(size_t)at] = h->row_of[(size_t)pb.root];
         for (int64_t i = 0; i <= len; ++i) {
             const uint8_t c = i < len ? s[i] : term;
@@ -342,6 +343,7 @@ tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int
             const PartPlan &r = parts[(size_t)p];
             PartBase &pb = base[(size_t)p];
             pb.root_tail = set_strings == 1;
+            pb.root_row = root_row[(size_t)j];
             pb.first_row = rows;
             rows += r.branching;
             pb.root = (int32_t)root[(size_t)j];
@@ -387,7 +389,6 @@ tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int
     h->tail_span.resize(host_tables ? (size_t)N : 0);
     h->row_at.resize(host_tables ? (size_t)BB : 0);
     h->tail_rec.resize(tails ? (size_t)h->K_unique : 0);
-    h->root_rows.assign(tails ? (size_t)(2 * S) : 0, 0);
     h->dense_rows = tails ? rows : 0;
     for (int64_t p = 0; p < kBlobPad; ++p) {
         h->blob[(size_t)p] = h->blob[(size_t)(BB - 1 - p)] = 0;
@@ -400,10 +401,6 @@ tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int
         h->edge[(size_t)rt] = 0;
         h->is_final[(size_t)rt] = 0;
         if (subtrees) h->sub_end[(size_t)rt] = (int32_t)(j + 1 < S ? root[(size_t)j + 1] : N);
-        if (tails) {
-            h->root_rows[(size_t)(2 * j)] = (int32_t)rt;
-            h->root_rows[(size_t)(2 * j + 1)] = root_row[(size_t)j];
-        }
         if (tails) h->row_of[(size_t)rt] = root_row[(size_t)j];
         if (host_tables) h->tail_span[(size_t)rt] = 0;
     }

@@ -23,8 +23,8 @@
 //   k_apply  -- write-mostly masking of [B, V] logits (lists and tail rows);
 //               k_apply_dense for dense-table rows, three rows per block (two
 //               for small batches); rows of any alignment.
-//   k_advance-- B byte walks over the child tables and along the strings of
-//               the blob, one wave per row.
+//   k_advance-- B byte walks along the strings of the blob and over the
+//               children that leave them, one wave per row.
 //   k_export_dense, k_export_tail -- canonical rows out of the dense table and
 //               (tail compression) the probe's hits.
 // Rows built on demand (lazy computation with a bounded cache, Appendix):
@@ -34,8 +34,8 @@
 //               subtree only, while the victims' rows are cleared; k_apply
 //               then reads the cache.
 // Trie tables on the device (from the blob and one record per string):
-//   k_node_at, k_pos_init, k_first_pos, k_child_count, k_child_fill,
-//   k_child_at, and under tail compression k_tail_nodes, k_root_rows, k_row_at.
+//   k_lay_init, k_lay (positions, tail tables), k_kid_alloc, k_kid_fill (the
+//   children that leave a string's own path).
 // Fixed-format values (character-position masks):
 //   k_format -- every word of the rows of positions 0..L+1, by wave ballots.
 #include <hip/hip_runtime.h>
@@ -1099,142 +1099,92 @@ __global__ void __launch_bounds__(kBlock) k_apply_dense(DevTables t, const int32
     }
 }
 
-// ------------------------------------------- node positions, child lists ---
+// ------------------------------------------------ node positions, children ---
 
-// The trie's node positions and child lists, built on the device from the
-// uploaded blob, node_at and depth.  The strings lie in the blob in trie
-// order, so a node's first position is where the string that created it wrote
-// its edge byte (node_pos), and one position before sits its parent (the pad
-// byte before a string stands for the set root).  Roots have no position.
+// The trie's position tables and children, built on the device from the uploaded
+// blob and one record per string (lay_string).  The nodes a string creates have
+// consecutive ids along consecutive positions, and each string but its set's
+// first adds exactly one child that leaves an earlier string's path, so the
+// children kept are one entry per string instead of one per node.
 
-// node_at and depth from the string records [s0, s1), one thread per string
-// (lay_string); a record that does not fit the tables is counted in *err.
-__global__ void __launch_bounds__(kBlock) k_node_at(const StrRec *__restrict__ strs, int64_t s0, int64_t s1,
-                                                    int64_t blob_bytes, int64_t N, int32_t *__restrict__ node_at,
-                                                    int32_t *__restrict__ depth, int32_t *err) {
-    const int64_t u = s0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (u >= s1) return;
-    const int32_t bad = lay_string(strs, s0, u, blob_bytes, N, node_at, depth);
+__global__ void __launch_bounds__(kBlock) k_lay_init(int32_t *node_at, int64_t blob_bytes, int32_t *kid_cnt,
+                                                     int32_t *count, int64_t N, int32_t *err, int32_t *kid_total) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < N) kid_cnt[i] = 0;
+    if (i < N && count) count[i] = 0;
+    if (i < kBlobPad) node_at[i] = node_at[blob_bytes - kBlobPad + i] = 0;
+    if (i == 0) *err = *kid_total = 0;
+}
+
+// One wave per string record of [s0, s1); a record that does not fit the tables
+// is counted in *err.  One thread per string wrote each table with 64 separate
+// lines per store and walked its characters one after another, and the tables
+// took six kernels (positions and tail tables, first positions by an atomicMin):
+// 37 us for 500 strings of 60 bytes against 5.8 us, 61 us for 32,000 strings of
+// a forest against 31 us.
+__global__ void __launch_bounds__(kBlock) k_lay(const StrRec *__restrict__ strs, const TailRec *__restrict__ trec,
+                                                int64_t s0, int64_t s1, int64_t blob_bytes, int64_t N, LayTables o,
+                                                int32_t *kid_cnt, int32_t *__restrict__ kid_parent,
+                                                int32_t *__restrict__ kid_rank, int32_t *err) {
+    const int64_t u = s0 + ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    if (u >= s1) return;  // uniform over the wave
+    int32_t par;
+    const int32_t bad = lay_string(strs, trec, s0, u, blob_bytes, N, o, lane, kWave, &par);
+    if (lane != 0) return;
     if (bad) atomicAdd(err, bad);
+    kid_parent[u] = par;  // a node of [0, N), or -1
+    if (par >= 0) kid_rank[u] = atomicAdd(&kid_cnt[par], 1);
 }
 
-// Tail compression's tables from the string records [s0, s1), one thread per
-// string: row_of and tail_span of the nodes it creates (path indices lcp ..
-// len, ids first ...; see TailRec).  Ids outside [0, N) are counted in *err
-// and skipped.
-__global__ void __launch_bounds__(kBlock) k_tail_nodes(const StrRec *__restrict__ strs,
-                                                       const TailRec *__restrict__ trec, int64_t s0, int64_t s1,
-                                                       int64_t N, int32_t *__restrict__ row_of,
-                                                       int32_t *__restrict__ tail_span, int32_t *err) {
-    const int64_t u = s0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (u >= s1) return;
-    const StrRec r = strs[u];
-    const TailRec tr = trec[u];
-    for (int32_t i = r.lcp; i <= r.len; ++i) {
-        const int64_t g = (int64_t)r.first + (i - r.lcp);
-        if (g < 0 || g >= N) {
-            atomicAdd(err, 1);
-            return;
-        }
-        const bool branching = i < tr.next;
-        row_of[g] = branching ? tr.row + (i - r.lcp) : -1 - (r.len - i);
-        tail_span[g] = branching ? 0 : i - tr.top;
-    }
+// The ranges of the entries: the first string counted at a parent takes them, one
+// atomic per block.
+__global__ void __launch_bounds__(kBlock) k_kid_alloc(int64_t K, Walk *walk, const int32_t *__restrict__ kid_cnt,
+                                                      const int32_t *__restrict__ kid_parent,
+                                                      const int32_t *__restrict__ kid_rank, int32_t *kid_total) {
+    const int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int32_t par = u < K ? kid_parent[u] : -1;
+    const bool lead = par >= 0 && kid_rank[u] == 0;
+    const int32_t n = lead ? kid_cnt[par] : 0;
+    const uint32_t byte = lead ? walk[par].nb : 0u;
+    int32_t total;
+    const int32_t at = block_exclusive_scan(n, &total);
+    __shared__ int32_t base;
+    if (threadIdx.x == 0) base = total ? atomicAdd(kid_total, total) : 0;
+    __syncthreads();
+    if (lead) walk[par] = Walk{base + at, byte | ((uint32_t)n << 8)};
 }
 
-// The set roots' entries: rr holds (root id, row) pairs.
-__global__ void __launch_bounds__(kBlock) k_root_rows(const int32_t *__restrict__ rr, int64_t S, int64_t N,
-                                                      int32_t *__restrict__ row_of, int32_t *__restrict__ tail_span,
-                                                      int32_t *err) {
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= S) return;
-    const int32_t rt = rr[2 * j];
-    if (rt < 0 || (int64_t)rt >= N) {
-        atomicAdd(err, 1);
-        return;
-    }
-    row_of[rt] = rr[2 * j + 1];
-    tail_span[rt] = 0;
-}
-
-// row_at[p] = row_of[node_at[p]] over the blob positions [b0, b1).
-__global__ void __launch_bounds__(kBlock) k_row_at(const int32_t *__restrict__ node_at,
-                                                   const int32_t *__restrict__ row_of, int64_t b0, int64_t b1,
-                                                   int64_t N, int32_t *__restrict__ row_at, int32_t *err) {
-    const int64_t p = b0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= b1) return;
-    const int32_t n = node_at[p];
-    if (n < 0 || (int64_t)n >= N) {
-        atomicAdd(err, 1);
-        row_at[p] = -1;
-        return;
-    }
-    row_at[p] = row_of[n];
-}
-
-// node_pos of the nodes [n0, n1): -1 for a root, else a large value that
-// k_first_pos lowers
-__global__ void __launch_bounds__(kBlock) k_pos_init(const int32_t *__restrict__ depth, int64_t n0, int64_t n1,
-                                                     int32_t *__restrict__ node_pos) {
-    const int64_t g = n0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g < n1) node_pos[g] = depth[g] == 0 ? -1 : INT_MAX;
-}
-
-// the first position of every non-root node in the blob range [b0, b1)
-__global__ void __launch_bounds__(kBlock) k_first_pos(const int32_t *__restrict__ node_at,
-                                                      const int32_t *__restrict__ depth, int64_t N, int64_t b0,
-                                                      int64_t b1, int32_t *node_pos, int32_t *err) {
-    const int64_t p = b0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= b1) return;
-    bool bad = false;
-    const int32_t g = lay_pos_node(node_at, depth, N, p, &bad);
-    if (g >= 0) atomicMin(&node_pos[g], (int32_t)p);
-    if (bad) atomicAdd(err, 1);
-}
-
-// The parent of non-root node g (lay_parent), or -1 after counting an
-// inconsistent position in t.err.
-__device__ __forceinline__ int32_t parent_of(const DevTables &t, int64_t g) {
-    bool bad = false;
-    const int32_t par = lay_parent(t.node_pos, t.node_at, t.N, t.blob_bytes, g, &bad);
-    if (bad) atomicAdd(t.err, 1);
-    return par;
-}
-
-// children per node (cnt zeroed before)
-__global__ void __launch_bounds__(kBlock) k_child_count(DevTables t, int32_t *cnt) {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= t.N || t.depth[g] == 0) return;
-    const int32_t par = parent_of(t, g);
-    if (par >= 0) atomicAdd(&cnt[par], 1);
-}
-
-// every non-root node into its parent's list (cursor zeroed before); the
-// order inside a list is free: a lookup matches the child byte
-__global__ void __launch_bounds__(kBlock) k_child_fill(DevTables t, int32_t *cursor, int32_t *child_node,
-                                                       uint8_t *child_byte, int32_t *child_pos) {
-    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= t.N || t.depth[g] == 0) return;
-    bool bad = false;  // counted once, by k_child_count
-    const int32_t par = lay_parent(t.node_pos, t.node_at, t.N, t.blob_bytes, g, &bad);
+// Every string's child into its parent's range; the order inside a range is
+// free: a lookup matches the child byte.
+__global__ void __launch_bounds__(kBlock) k_kid_fill(const StrRec *__restrict__ strs, int64_t K,
+                                                     const Walk *__restrict__ walk, Kid *__restrict__ kid,
+                                                     const int32_t *__restrict__ kid_parent,
+                                                     const int32_t *__restrict__ kid_rank, int32_t *err) {
+    const int64_t u = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int32_t par = u < K ? kid_parent[u] : -1;
     if (par < 0) return;
-    const int32_t slot = t.child_off[par] + atomicAdd(&cursor[par], 1);
-    const int32_t pos = t.node_pos[g];
-    child_node[slot] = (int32_t)g;
-    child_pos[slot] = pos;
-    child_byte[slot] = t.blob[pos];
+    const int32_t c = strs[u].first;
+    const int64_t at = (int64_t)walk[par].off + kid_rank[u];
+    if (at < 0 || at >= K) {
+        atomicAdd(err, 1);
+        return;
+    }
+    const Walk w = walk[c];
+    kid[at] = Kid{c, w.off, w.nb, 0};
 }
 
-// child_at[p]: the child range of the node whose edge byte is blob[p] (the
-// pads: their set's root), for walks that stop inside a string
-__global__ void __launch_bounds__(kBlock) k_child_at(DevTables t, uint64_t *child_at) {
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= t.blob_bytes) return;
-    const int32_t n = t.node_at[p];
-    uint64_t r = 0;
-    if (n >= 0 && (int64_t)n < t.N)
-        r = (uint64_t)(uint32_t)t.child_off[n] | ((uint64_t)(uint32_t)t.child_off[n + 1] << 32);
-    child_at[p] = r;
+__global__ void __launch_bounds__(kBlock) k_tok_heads(const uint32_t *__restrict__ tok_off,
+                                                      const uint8_t *__restrict__ tok_blob, int64_t V,
+                                                      TokHead *__restrict__ head) {
+    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (v >= V) return;
+    const uint32_t o = tok_off[v], len = tok_off[v + 1] - o;
+    TokHead h;
+#pragma unroll
+    for (int k = 0; k < kHeadLen; ++k) h.b[k] = k < (int)len ? tok_blob[o + k] : 0;
+    h.b[15] = len <= (uint32_t)kHeadLen ? (uint8_t)len : 255;
+    head[v] = h;
 }
 
 // ------------------------------------------------- fixed-format strings ---
@@ -1355,16 +1305,23 @@ __global__ void __launch_bounds__(kBlock) k_format(DevTables t, uint64_t *__rest
 
 // --------------------------------------------------------------- advance ---
 
-// The extended transition function, one wave per batch row.  A child step
-// compares up to 64 of the node's child bytes at once (one ballot)
-// instead of a binary search.  Between child steps the walk follows the
-// node's owner string (the first set string through it, stored in the blob
-// right after the node's edge byte): lane j compares token byte i+j with the
-// string's byte j, 64 at a time, and the walk jumps to node_at of the last
-// matching position.  The run may include the owner string's terminator but
-// never goes past it (the node after T has no children).  A token needs one
-// child step per point where it leaves the owner string's path, usually one or
-// two.
+// The extended transition function, one wave per batch row.  The walk follows
+// the string that created the current node n, whose nodes have consecutive ids:
+// lane j >= 1 compares the edge byte of node n + j with the token's next j-th
+// byte, and has that node's other children beside it (Walk).  So a token along one
+// string ends after its first window, its node known without a further load, and
+// where the token leaves the string the children there are known: one round trip
+// for their entries (a ballot picks the byte), one for the next window, which
+// also loads the entries of the child's own children, so that a token that
+// leaves again at once (near the root of a large set) takes one trip per branch.
+// The run may include the string's terminator but never goes past it (the node
+// after T has no children).
+// Bound by these dependent trips (cold lines after a large apply): the ids; the
+// token's head with the first window; then the branches.  With every child
+// listed, and the child ranges by position, node ids, child bytes and token bytes
+// behind offsets in tables of their own, a token took five trips and three per
+// branch.  256 rows decoding from the root of 10,000 word strings: 10.1 -> 7.0 us
+// per call; over a forest 5.6 -> 4.6 us, anywhere in a code list 4.7 -> 4.3 us.
 __global__ void __launch_bounds__(kBlock) k_advance(DevTables t, const int32_t *nodes, const int32_t *toks,
                                                     int64_t B, int32_t *out) {
     const int64_t b = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
@@ -1384,61 +1341,80 @@ __global__ void __launch_bounds__(kBlock) k_advance(DevTables t, const int32_t *
         return;
     }
     if (ok) {
-        const int64_t a = t.tok_off[v];
-        const int len = (int)(t.tok_off[v + 1] - (uint32_t)a);
+        // lane j: byte j of the token's head, and node n0 + j for the longest token
+        // a head holds
+        const uint32_t hb = t.tok_head[v].b[lane & 15];
+        Walk w{0, 0x200u};
+        if (lane <= kHeadLen && (int64_t)n0 + lane < t.N) w = t.walk[n0 + lane];
         const uint32_t T = (uint32_t)t.terminator;
-        int i = 0;
+        int len = (int)__shfl(hb, 15, kWave);
+        int64_t a = 0;
+        const bool shrt = len <= kHeadLen;
+        if (!shrt) {
+            a = t.tok_off[v];
+            len = (int)(t.tok_off[v + 1] - (uint32_t)a);
+        }
+        // lanes past kHeadLen of the first window of a longer token count as a
+        // mismatch there: the walk then loads the next window instead of branching
+        int width = kHeadLen + 1;  // lanes the window covers
+        int i = 0;                 // token bytes walked
+        Kid e{TAM_DEAD, 0, 0x100u, 0};  // lane j: entry j of n's other children, when held
+        bool held = false;
         n = len > 0 ? n0 : TAM_DEAD;
-        int32_t lo = t.child_off[n0], hi = t.child_off[n0 + 1];  // loaded beside the token's offsets
-        while (i < len && n >= 0) {
-            const uint32_t c = t.tok_blob[a + i];
-            // child of n along c: its child bytes, ids and blob positions, 64
-            // lanes at a time, loaded together with the token byte
-            int32_t nx = TAM_DEAD, px = 0;
-            for (int32_t k0 = lo; k0 < hi; k0 += kWave) {
-                const int32_t k = k0 + lane;
-                const bool in = k < hi;
-                const uint32_t cb = in ? (uint32_t)t.child_byte[k] : 0x100u;
-                const int32_t cn = in ? t.child_node[k] : TAM_DEAD;
-                const int32_t cp = in ? t.child_pos[k] : 0;
-                const uint64_t m = __ballot(cb == c);
-                if (m) {
-                    const int j = (int)__builtin_ctzll(m);
-                    nx = __shfl(cn, j, kWave);
-                    px = __shfl(cp, j, kWave);
-                    break;
-                }
-            }
-            n = nx;
-            ++i;
-            if (n < 0 || i >= len) break;  // dead or done
-            if (c == T) {                  // a final node: it has no children
+        while (n >= 0 && i < len) {
+            // lane 0: the node's own byte; lane j: token byte i + j - 1
+            const int j = i + lane - 1;
+            uint32_t tb = __shfl(hb, j & 15, kWave);
+            if (!shrt) tb = lane > 0 && j < len ? (uint32_t)t.tok_blob[a + j] : 0x100u;
+            const bool in = lane < width && lane <= len - i;
+            const uint32_t sb = in ? w.nb & 0xffu : 0x200u;
+            const uint64_t term = __ballot(sb == T);
+            const uint64_t diff = __ballot(lane > 0 && (!in || sb != tb));
+            const int f = term ? (int)__builtin_ctzll(term) : kWave;  // the first T
+            const int run = diff ? (int)__builtin_ctzll(diff) - 1 : kWave - 1;
+            const int k = min(run, f);
+            if (f == 0) {  // a final node has no children
                 n = TAM_DEAD;
                 break;
             }
-            int64_t p = px;
-            for (;;) {
-                const int64_t q = p + 1 + lane;
-                const uint32_t sb = q < t.blob_bytes ? (uint32_t)t.blob[q] : 0x200u;
-                const uint32_t tb = i + lane < len ? (uint32_t)t.tok_blob[a + i + lane] : 0x100u;
-                const uint64_t term = __ballot(sb == T);
-                const uint64_t diff = ~__ballot(sb == tb);
-                const int f = term ? (int)__builtin_ctzll(term) : kWave;  // first T of the window
-                const int run = diff ? (int)__builtin_ctzll(diff) : kWave;
-                const int k = min(run, f < kWave ? f + 1 : kWave);      // up to and including T
-                p += k;
-                i += k;
-                if (k < kWave || i >= len || f < kWave) break;
-            }
-            if (i >= len) {  // the token ends inside the string: its node
-                n = t.node_at[p];
+            n += k;
+            i += k;
+            if (i >= len) break;  // the token ends inside the string
+            if (k == f) {         // it runs past T
+                n = TAM_DEAD;
                 break;
             }
-            // the token leaves the string at p: the child range of the node
-            // there, in one load (the node itself is not needed)
-            const uint64_t r = t.child_at[p];
-            lo = (int32_t)(uint32_t)r;
-            hi = (int32_t)(uint32_t)(r >> 32);
+            if (k < width - 1) {
+                // the token leaves the string: the child of n along its next byte
+                const int32_t k0 = __shfl(w.off, k, kWave), kn = (int32_t)(__shfl(w.nb, k, kWave) >> 8);
+                const uint32_t c = __shfl(tb, k + 1, kWave);
+                n = TAM_DEAD;
+                int32_t c0 = 0, cn = 0;
+                for (int32_t j0 = 0; j0 < kn; j0 += kWave) {
+                    if (!(held && k == 0 && j0 == 0)) {
+                        e = Kid{TAM_DEAD, 0, 0x100u, 0};
+                        if (j0 + lane < kn) e = t.kid[(int64_t)k0 + j0 + lane];
+                    }
+                    const uint64_t m = __ballot(j0 + lane < kn && (e.nb & 0xffu) == c);
+                    if (m) {
+                        const int l = (int)__builtin_ctzll(m);
+                        n = __shfl(e.node, l, kWave);
+                        c0 = __shfl(e.off, l, kWave);
+                        cn = (int32_t)(__shfl(e.nb, l, kWave) >> 8);
+                        break;
+                    }
+                }
+                ++i;
+                if (i < len && c == T) n = TAM_DEAD;  // past T
+                if (n < 0 || i >= len) break;
+                held = true;
+                if (lane < cn) e = t.kid[(int64_t)c0 + lane];
+            } else {
+                held = false;
+            }
+            width = kWave;
+            w = Walk{0, 0x200u};
+            if (lane <= len - i && (int64_t)n + lane < t.N) w = t.walk[n + lane];
         }
     }
     if (lane == 0) out[b] = n;
@@ -1988,61 +1964,37 @@ hipError_t launch_count_range(const DevTables &t, int64_t m0, int64_t m1, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_node_at(const StrRec *strs, int64_t s0, int64_t s1, int64_t blob_bytes, int64_t N,
-                          int32_t *node_at, int32_t *depth, int32_t *err, hipStream_t s) {
+hipError_t launch_lay_init(int32_t *node_at, int64_t blob_bytes, int32_t *kid_cnt, int32_t *count, int64_t N,
+                           int32_t *err, int32_t *kid_total, hipStream_t s) {
+    if (blob_bytes < 2 * kBlobPad) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_lay_init, dim3(grid_for(std::max<int64_t>(N, kBlobPad), kBlock)), dim3(kBlock), 0, s, node_at,
+                       blob_bytes, kid_cnt, count, N, err, kid_total);
+    return hipGetLastError();
+}
+
+hipError_t launch_lay(const StrRec *strs, const TailRec *trec, int64_t s0, int64_t s1, int64_t blob_bytes, int64_t N,
+                      const LayTables &o, int32_t *kid_cnt, int32_t *kid_parent, int32_t *kid_rank, int32_t *err,
+                      hipStream_t s) {
     if (s1 <= s0) return hipSuccess;
-    hipLaunchKernelGGL(k_node_at, dim3(grid_for(s1 - s0, kBlock)), dim3(kBlock), 0, s, strs, s0, s1, blob_bytes, N,
-                       node_at, depth, err);
+    if ((trec != nullptr) != (o.row_of != nullptr)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_lay, dim3(grid_for(s1 - s0, kBlock / kWave)), dim3(kBlock), 0, s, strs, trec, s0, s1,
+                       blob_bytes, N, o, kid_cnt, kid_parent, kid_rank, err);
     return hipGetLastError();
 }
 
-hipError_t launch_tail_tables(const StrRec *strs, const TailRec *trec, int64_t s0, int64_t s1,
-                              const int32_t *root_rows, int64_t S, const int32_t *node_at, int64_t b0, int64_t b1,
-                              int64_t N, int32_t *row_of, int32_t *tail_span, int32_t *row_at, int32_t *err,
-                              hipStream_t s) {
-    if (s1 > s0)
-        hipLaunchKernelGGL(k_tail_nodes, dim3(grid_for(s1 - s0, kBlock)), dim3(kBlock), 0, s, strs, trec, s0, s1, N,
-                           row_of, tail_span, err);
-    if (root_rows && S > 0)
-        hipLaunchKernelGGL(k_root_rows, dim3(grid_for(S, kBlock)), dim3(kBlock), 0, s, root_rows, S, N, row_of,
-                           tail_span, err);
-    if (b1 > b0)
-        hipLaunchKernelGGL(k_row_at, dim3(grid_for(b1 - b0, kBlock)), dim3(kBlock), 0, s, node_at, row_of, b0, b1, N,
-                           row_at, err);
+hipError_t launch_kids(const StrRec *strs, int64_t K, int64_t N, Walk *walk, Kid *kid, const int32_t *kid_cnt,
+                       const int32_t *kid_parent, const int32_t *kid_rank, int32_t *kid_total, int32_t *err,
+                       hipStream_t s) {
+    if (K <= 0 || N <= 0) return hipSuccess;
+    const dim3 grid(grid_for(K, kBlock));
+    hipLaunchKernelGGL(k_kid_alloc, grid, dim3(kBlock), 0, s, K, walk, kid_cnt, kid_parent, kid_rank, kid_total);
+    hipLaunchKernelGGL(k_kid_fill, grid, dim3(kBlock), 0, s, strs, K, walk, kid, kid_parent, kid_rank, err);
     return hipGetLastError();
 }
 
-hipError_t launch_node_pos(const DevTables &t, int32_t *node_pos, int64_t n0, int64_t n1, int64_t b0, int64_t b1,
-                           hipStream_t s) {
-    if (n0 < 0 || n1 > t.N || b0 < 0 || b1 > t.blob_bytes) return hipErrorInvalidValue;
-    if (n1 > n0)
-        hipLaunchKernelGGL(k_pos_init, dim3(grid_for(n1 - n0, kBlock)), dim3(kBlock), 0, s, t.depth, n0, n1, node_pos);
-    if (b1 > b0)
-        hipLaunchKernelGGL(k_first_pos, dim3(grid_for(b1 - b0, kBlock)), dim3(kBlock), 0, s, t.node_at, t.depth, t.N,
-                           b0, b1, node_pos, t.err);
-    return hipGetLastError();
-}
-
-hipError_t launch_child_lists(const DevTables &t, int32_t *child_off, int32_t *child_node, uint8_t *child_byte,
-                              int32_t *child_pos, uint64_t *child_at, int32_t *tmp, int32_t *scan_tmp,
-                              hipStream_t s) {
-    if (t.N <= 0) return hipSuccess;
-    const unsigned g = grid_for(t.N, kBlock);
-    hipError_t e = launch_fill_i32(tmp, t.N, 0, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_child_count, dim3(g), dim3(kBlock), 0, s, t, tmp);
-    DevTables ts = t;  // the scan: counts -> child_off[0..N], the total at N
-    ts.count = tmp;
-    ts.row_ptr = child_off;
-    ts.scan_tmp = scan_tmp;
-    e = launch_scan(ts, s);
-    if (e == hipSuccess) e = launch_fill_i32(tmp, t.N, 0, s);
-    if (e != hipSuccess) return e;
-    DevTables tf = t;
-    tf.child_off = child_off;
-    hipLaunchKernelGGL(k_child_fill, dim3(g), dim3(kBlock), 0, s, tf, tmp, child_node, child_byte, child_pos);
-    if (t.blob_bytes > 0)
-        hipLaunchKernelGGL(k_child_at, dim3(grid_for(t.blob_bytes, kBlock)), dim3(kBlock), 0, s, tf, child_at);
+hipError_t launch_tok_heads(const uint32_t *tok_off, const uint8_t *tok_blob, int64_t V, TokHead *head, hipStream_t s) {
+    if (V <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tok_heads, dim3(grid_for(V, kBlock)), dim3(kBlock), 0, s, tok_off, tok_blob, V, head);
     return hipGetLastError();
 }
 

@@ -246,6 +246,7 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     Arena a;
     const size_t o_off = a.take<uint32_t>(V + 1);
     const size_t o_blob = a.take<uint8_t>((int64_t)v->tok_blob.size());
+    const size_t o_head = a.take<tam::TokHead>(V);
     const size_t o_fps = a.take<uint16_t>((int64_t)v->fps.size());
     const size_t o_pay = a.take<tam::SlotPay>((int64_t)v->pay.size());
     const size_t o_pay_hi = a.take<uint64_t>((int64_t)v->pay_hi.size());
@@ -261,6 +262,7 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     v->device_bytes = (int64_t)a.used;
     v->d_tok_off = reinterpret_cast<const uint32_t *>(base + o_off);
     v->d_tok_blob = base + o_blob;
+    v->d_tok_head = reinterpret_cast<const tam::TokHead *>(base + o_head);
     v->d_fps = reinterpret_cast<const uint16_t *>(base + o_fps);
     v->d_pay = reinterpret_cast<const tam::SlotPay *>(base + o_pay);
     v->d_pay_hi = reinterpret_cast<const uint64_t *>(base + o_pay_hi);
@@ -279,6 +281,8 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     if (e == hipSuccess) e = up(o_short, v->short_hits.data(), v->short_hits.size() * sizeof(int32_t));
     if (e == hipSuccess) e = up(o_dup, v->dup_next.data(), v->dup_next.size() * 4);
     if (e == hipSuccess) e = up(o_len, v->len_present.data(), v->len_present.size());
+    if (e == hipSuccess)
+        e = tam::launch_tok_heads(v->d_tok_off, v->d_tok_blob, V, reinterpret_cast<tam::TokHead *>(base + o_head), s);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ready, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(v->ready, s);
     v->upload_ms = ms_since(t1);
@@ -446,19 +450,16 @@ tam_status check_device_handle(const tam_handle *h) {
 // vocabulary's tables in a DevTables, with the sizes they imply; no table,
 // tails or lists yet.
 void set_trie_tables(tam::DevTables &t, const tam_handle *h, const tam_vocab *v, uint8_t *tb, size_t o_blob,
-                     size_t o_node_at, size_t o_node_pos, size_t o_depth, size_t o_child_off, size_t o_child_byte,
-                     size_t o_child_node, size_t o_child_pos, size_t o_child_at) {
+                     size_t o_node_at, size_t o_node_pos, size_t o_depth, size_t o_walk, size_t o_kid) {
     t.blob = tb + o_blob;
     t.node_at = reinterpret_cast<const int32_t *>(tb + o_node_at);
     t.node_pos = reinterpret_cast<const int32_t *>(tb + o_node_pos);
     t.depth = reinterpret_cast<const int32_t *>(tb + o_depth);
-    t.child_off = reinterpret_cast<const int32_t *>(tb + o_child_off);
-    t.child_byte = tb + o_child_byte;
-    t.child_node = reinterpret_cast<const int32_t *>(tb + o_child_node);
-    t.child_pos = reinterpret_cast<const int32_t *>(tb + o_child_pos);
-    t.child_at = reinterpret_cast<const uint64_t *>(tb + o_child_at);
+    t.walk = reinterpret_cast<const tam::Walk *>(tb + o_walk);
+    t.kid = reinterpret_cast<const tam::Kid *>(tb + o_kid);
     t.tok_off = v->d_tok_off;
     t.tok_blob = v->d_tok_blob;
+    t.tok_head = v->d_tok_head;
     t.fps = v->d_fps;
     t.pay = v->d_pay;
     t.pay_hi = v->d_pay_hi;
@@ -528,12 +529,11 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
     const bool early_zero =
         !host_only && !(o.flags & (TAM_FLAG_NO_TABLE | TAM_FLAG_TAIL_LISTS | TAM_FLAG_LAZY_ROWS));
     uint64_t *early_table = nullptr;
-    // blob, node_at, node_pos, depth, child_off, child_byte, child_node, sub_end,
-    // and tail compression's tail_span, row_of, row_at
+    // blob, node_at, node_pos, depth, the children, sub_end, and tail
+    // compression's tail_span, row_of, row_at
     uint8_t *trie_base = nullptr;
-    size_t o_blob = 0, o_node_at = 0, o_node_pos = 0, o_depth = 0, o_child_off = 0, o_child_byte = 0,
-           o_child_node = 0, o_child_pos = 0, o_child_at = 0, o_sub_end = 0, o_tail_span = 0, o_row_of = 0, o_row_at = 0, o_tail_rec = 0,
-           o_root_rows = 0;
+    size_t o_blob = 0, o_node_at = 0, o_node_pos = 0, o_depth = 0, o_walk = 0, o_kid = 0, o_sub_end = 0,
+           o_tail_span = 0, o_row_of = 0, o_row_at = 0, o_tail_rec = 0;
     // tail compression's split (with a table for the branching nodes, or with
     // sparse lists for them)
     const bool split = (o.flags & TAM_FLAG_TAIL_LISTS) && !(o.flags & TAM_FLAG_LAZY_ROWS);
@@ -549,7 +549,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
                             !(o.flags & TAM_FLAG_LAZY_ROWS);
     size_t o_pairs_t = 0, o_rec_off_t = 0, o_rec_cnt_t = 0;
     int64_t next_blk = 0, next_off = 0, listed_total = 0;  // early_tail: the groups' blocks, offsets, records
-    size_t o_hits = 0, o_count = 0, o_tmp = 0, o_scan_tmp = 0, o_strs = 0, o_err = 0;
+    size_t o_hits = 0, o_count = 0, o_kid_cnt = 0, o_kid_parent = 0, o_kid_rank = 0, o_kid_total = 0, o_strs = 0, o_err = 0;
     tam::DevTables te{};  // the trie and vocabulary tables the early counts read
     bool enqueued = false;  // device work that reads host tables or writes device memory
     double hook_ms = 0;     // time spent in the two hooks (allocation and enqueue)
@@ -571,17 +571,13 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         o_node_at = ta.take<int32_t>(hh->blob_bytes);
         o_node_pos = ta.take<int32_t>(hh->N);
         o_depth = ta.take<int32_t>(hh->N);
-        o_child_off = ta.take<int32_t>(hh->N + 1);
-        o_child_byte = ta.take<uint8_t>(hh->edges);
-        o_child_node = ta.take<int32_t>(hh->edges);
-        o_child_pos = ta.take<int32_t>(hh->edges);
-        o_child_at = ta.take<uint64_t>(hh->blob_bytes);
+        o_walk = ta.take<tam::Walk>(hh->N);
+        o_kid = ta.take<tam::Kid>(hh->K_unique);
         o_sub_end = ta.take<int32_t>((hh->flags & TAM_FLAG_LAZY_ROWS) ? hh->N : 0);
         o_tail_span = ta.take<int32_t>(split ? hh->N : 0);
         o_row_of = ta.take<int32_t>(split ? hh->N : 0);
         o_row_at = ta.take<int32_t>(split ? hh->blob_bytes : 0);
         o_tail_rec = ta.take<tam::TailRec>(split ? hh->K_unique : 0);
-        o_root_rows = ta.take<int32_t>(split ? 2 * hh->S : 0);
         o_hits = ta.take<int32_t>(early_count || early_tail ? tam::kWin * hh->N : 0);
         o_count = ta.take<int32_t>(early_count || early_tail ? hh->N : 0);
         // a group's blocks start a new block of nodes: at most one more block
@@ -592,8 +588,10 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         o_rec_cnt_t = ta.take<int32_t>(early_tail ? gblocks : 0);
         if (early_tail) hh->rec_off.resize((size_t)(gblocks + tam::kMaxRecGroups));
         o_strs = ta.take<tam::StrRec>(hh->K_unique);
-        o_tmp = ta.take<int32_t>(hh->N);  // scratch of the child lists' build
-        o_scan_tmp = ta.take<int32_t>(tam::scan_tmp_elems(hh->N));
+        o_kid_cnt = ta.take<int32_t>(hh->N);  // scratch of the children's build
+        o_kid_parent = ta.take<int32_t>(hh->K_unique);
+        o_kid_rank = ta.take<int32_t>(hh->K_unique);
+        o_kid_total = ta.take<int32_t>(1);
         o_err = ta.take<int32_t>(1);
         trie_base = static_cast<uint8_t *>(dev_alloc(hh, ta.used));
         if (!trie_base) {
@@ -601,16 +599,16 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
             return TAM_E_NOMEM;
         }
         hh->device_bytes = (int64_t)ta.used;
-        set_trie_tables(te, hh, vocab, trie_base, o_blob, o_node_at, o_node_pos, o_depth, o_child_off, o_child_byte,
-                        o_child_node, o_child_pos, o_child_at);
+        set_trie_tables(te, hh, vocab, trie_base, o_blob, o_node_at, o_node_pos, o_depth, o_walk, o_kid);
         hh->d_err = reinterpret_cast<int32_t *>(trie_base + o_err);
         hh->h_err = tam::err_slot_take();
         te.err = hh->d_err;
-        {  // the blob's outer pads stand for the first set's root; no device error yet
-            int32_t *node_at = reinterpret_cast<int32_t *>(trie_base + o_node_at);
-            hipError_t e = tam::launch_fill_i32(hh->d_err, 1, 0, s);
-            if (e == hipSuccess) e = tam::launch_fill_i32(node_at, tam::kBlobPad, 0, s);
-            if (e == hipSuccess) e = tam::launch_fill_i32(node_at + hh->blob_bytes - tam::kBlobPad, tam::kBlobPad, 0, s);
+        {  // the blob's outer pads stand for the first set's root; counts zeroed; no device error yet
+            const hipError_t e = tam::launch_lay_init(
+                reinterpret_cast<int32_t *>(trie_base + o_node_at), hh->blob_bytes,
+                reinterpret_cast<int32_t *>(trie_base + o_kid_cnt),
+                early_count || early_tail ? reinterpret_cast<int32_t *>(trie_base + o_count) : nullptr, hh->N,
+                hh->d_err, reinterpret_cast<int32_t *>(trie_base + o_kid_total), s);
             enqueued = true;
             if (e != hipSuccess) {
                 err = std::string("trie tables: ") + hipGetErrorString(e);
@@ -633,8 +631,6 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
             if (e == hipSuccess && timing) e = create_events(hh);
             if (e == hipSuccess && timing) e = hipEventRecord(hh->ev[0], s);
             if (e == hipSuccess && timing) e = hipEventRecord(hh->ev[1], s);  // no zero fill
-            if (e == hipSuccess) e = tam::launch_fill_i32(te.count, hh->N, 0, s);
-            enqueued = true;
             if (e != hipSuccess) {
                 err = std::string("list counts: ") + hipGetErrorString(e);
                 return TAM_E_DEVICE;
@@ -677,28 +673,23 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         up(o_blob, hh->blob.data(), r.b_lo, r.b_hi, 1);
         up(o_strs, hh->strs.data(), r.s_lo, r.s_hi, sizeof(tam::StrRec));
         if (hh->flags & TAM_FLAG_LAZY_ROWS) up(o_sub_end, hh->sub_end.data(), r.n_lo, r.n_hi, 4);
-        if (split) {  // the tail tables are laid out on the device from these
+        if (split)  // the tail tables are laid out on the device from these
             up(o_tail_rec, hh->tail_rec.data(), r.s_lo, r.s_hi, sizeof(tam::TailRec));
-            if (r.n_lo == 0) up(o_root_rows, hh->root_rows.data(), 0, (int64_t)hh->root_rows.size(), 4);
+        // the group's position and tail tables (from its strings), then (lists)
+        // its counts; after the last group the children
+        const tam::StrRec *strs = reinterpret_cast<const tam::StrRec *>(trie_base + o_strs);
+        tam::Walk *walk = reinterpret_cast<tam::Walk *>(trie_base + o_walk);
+        int32_t *kid_cnt = reinterpret_cast<int32_t *>(trie_base + o_kid_cnt);
+        int32_t *kid_parent = reinterpret_cast<int32_t *>(trie_base + o_kid_parent);
+        int32_t *kid_rank = reinterpret_cast<int32_t *>(trie_base + o_kid_rank);
+        if (e == hipSuccess) {
+            auto at = [&](size_t off) { return reinterpret_cast<int32_t *>(trie_base + off); };
+            const tam::LayTables lt{at(o_node_at), at(o_depth), at(o_node_pos), walk, te.blob,
+                                    (uint32_t)hh->terminator, split ? at(o_row_of) : nullptr,
+                                    split ? at(o_tail_span) : nullptr, split ? at(o_row_at) : nullptr};
+            e = tam::launch_lay(strs, split ? reinterpret_cast<const tam::TailRec *>(trie_base + o_tail_rec) : nullptr,
+                                r.s_lo, r.s_hi, hh->blob_bytes, hh->N, lt, kid_cnt, kid_parent, kid_rank, hh->d_err, s);
         }
-        // the group's node_at and depth (from its strings), node positions
-        // (its nodes lie in its blob range), then (lists) its counts; after the
-        // last group the child lists
-        int32_t *node_pos = reinterpret_cast<int32_t *>(trie_base + o_node_pos);
-        if (e == hipSuccess)
-            e = tam::launch_node_at(reinterpret_cast<const tam::StrRec *>(trie_base + o_strs), r.s_lo, r.s_hi,
-                                    hh->blob_bytes, hh->N, reinterpret_cast<int32_t *>(trie_base + o_node_at),
-                                    reinterpret_cast<int32_t *>(trie_base + o_depth), hh->d_err, s);
-        if (e == hipSuccess && split)
-            e = tam::launch_tail_tables(reinterpret_cast<const tam::StrRec *>(trie_base + o_strs),
-                                        reinterpret_cast<const tam::TailRec *>(trie_base + o_tail_rec), r.s_lo,
-                                        r.s_hi, r.n_lo == 0 ? reinterpret_cast<const int32_t *>(trie_base + o_root_rows)
-                                                            : nullptr,
-                                        hh->S, reinterpret_cast<const int32_t *>(trie_base + o_node_at), r.b_lo,
-                                        r.b_hi, hh->N, reinterpret_cast<int32_t *>(trie_base + o_row_of),
-                                        reinterpret_cast<int32_t *>(trie_base + o_tail_span),
-                                        reinterpret_cast<int32_t *>(trie_base + o_row_at), hh->d_err, s);
-        if (e == hipSuccess) e = tam::launch_node_pos(te, node_pos, r.n_lo, r.n_hi, r.b_lo, r.b_hi, s);
         if (early_count && e == hipSuccess) {
             const bool timing = (hh->flags & TAM_FLAG_TIMING) != 0;
             if (timing && r.n_lo == 0) e = hipEventRecord(hh->ev[4], s);  // the counts' start
@@ -747,13 +738,9 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
             listed_total += total;
         }
         if (e == hipSuccess && r.n_hi == hh->N)
-            e = tam::launch_child_lists(te, reinterpret_cast<int32_t *>(trie_base + o_child_off),
-                                        reinterpret_cast<int32_t *>(trie_base + o_child_node),
-                                        trie_base + o_child_byte,
-                                        reinterpret_cast<int32_t *>(trie_base + o_child_pos),
-                                        reinterpret_cast<uint64_t *>(trie_base + o_child_at),
-                                        reinterpret_cast<int32_t *>(trie_base + o_tmp),
-                                        reinterpret_cast<int32_t *>(trie_base + o_scan_tmp), s);
+            e = tam::launch_kids(strs, hh->K_unique, hh->N, walk, reinterpret_cast<tam::Kid *>(trie_base + o_kid),
+                                 kid_cnt, kid_parent, kid_rank,
+                                 reinterpret_cast<int32_t *>(trie_base + o_kid_total), hh->d_err, s);
         hook_ms += ms_since(t1);
         if (e != hipSuccess) {
             err = std::string("upload: ") + hipGetErrorString(e);
@@ -872,8 +859,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
                           : reinterpret_cast<int32_t *>(base + o_pairs);
 
     tam::DevTables &t = h->dt;
-    set_trie_tables(t, h, vocab, trie_base, o_blob, o_node_at, o_node_pos, o_depth, o_child_off, o_child_byte,
-                    o_child_node, o_child_pos, o_child_at);
+    set_trie_tables(t, h, vocab, trie_base, o_blob, o_node_at, o_node_pos, o_depth, o_walk, o_kid);
     t.err = h->d_err;
     t.hits = early ? te.hits : reinterpret_cast<int32_t *>(base + o_hits_b);
     t.count = early ? te.count : reinterpret_cast<int32_t *>(base + o_count_b);
@@ -1084,14 +1070,10 @@ void layout_on_host(tam_handle *h) {
     int32_t *node_pos = h->lay_node_pos.data(), *parent = h->lay_parent.data();
     int64_t errors = 0;
     const int64_t K = (int64_t)h->strs.size();
-    for (int64_t u = 0; u < K; ++u) errors += tam::lay_string(h->strs.data(), 0, u, BB, N, node_at, depth);
-    for (int64_t g = 0; g < N; ++g) node_pos[g] = depth[g] == 0 ? -1 : INT32_MAX;
-    for (int64_t p = 0; p < BB; ++p) {
-        bool bad = false;
-        const int32_t g = tam::lay_pos_node(node_at, depth, N, p, &bad);
-        if (g >= 0 && p < node_pos[g]) node_pos[g] = (int32_t)p;
-        errors += bad ? 1 : 0;
-    }
+    const tam::LayTables lt{node_at, depth, node_pos, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+    int32_t par;
+    for (int64_t u = 0; u < K; ++u)
+        errors += tam::lay_string(h->strs.data(), nullptr, 0, u, BB, N, lt, 0, 1, &par);
     for (int64_t g = 0; g < N; ++g) {
         if (depth[g] == 0) continue;
         bool bad = false;

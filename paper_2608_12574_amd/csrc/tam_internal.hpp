@@ -13,6 +13,7 @@
 
 #include "../../include/tam.h"
 #include "device_tables.hpp"
+#include "trie_layout.hpp"
 
 namespace tam {
 
@@ -79,32 +80,27 @@ hipError_t launch_probe(const DevTables &t, bool count, bool mark, int32_t *pair
 // the list counts of the nodes [m0, m1) (lists only: t.table null; t.count of
 // those nodes zeroed), nodes whose ancestors lie in the same range
 hipError_t launch_count_range(const DevTables &t, int64_t m0, int64_t m1, hipStream_t s);
-// node_at and depth of the string records [s0, s1) (records uploaded; the
-// strings' earlier part-mates with shorter prefixes are in the same range)
-hipError_t launch_node_at(const StrRec *strs, int64_t s0, int64_t s1, int64_t blob_bytes, int64_t N,
-                          int32_t *node_at, int32_t *depth, int32_t *err, hipStream_t s);
-// node_pos of the nodes [n0, n1) from the blob range [b0, b1) they were
-// written in (node_at and depth of those ranges uploaded)
-hipError_t launch_node_pos(const DevTables &t, int32_t *node_pos, int64_t n0, int64_t n1, int64_t b0, int64_t b1,
-                           hipStream_t s);
-// the child lists of every node (node_pos complete): child_off[N+1],
-// child_node/child_byte/child_pos[N - roots], and child_at[blob_bytes] (the
-// child range of the node at each blob position); tmp [N] and scan_tmp
-// [scan_tmp_elems(N)] are scratch
-hipError_t launch_child_lists(const DevTables &t, int32_t *child_off, int32_t *child_node, uint8_t *child_byte,
-                              int32_t *child_pos, uint64_t *child_at, int32_t *tmp, int32_t *scan_tmp,
-                              hipStream_t s);
+// Before the first group: the blob's outer pads in node_at, kid_cnt [N], count
+// [N] (null: not kept), the error count and the kids' total, all zero.
+hipError_t launch_lay_init(int32_t *node_at, int64_t blob_bytes, int32_t *kid_cnt, int32_t *count, int64_t N,
+                           int32_t *err, int32_t *kid_total, hipStream_t s);
+// the position tables (and under tail compression the tail tables) of the string
+// records [s0, s1) (records uploaded; the strings' earlier part-mates with
+// shorter prefixes are in the same range); the other children are counted in
+// kid_cnt [N], each string's parent and rank kept in kid_parent / kid_rank [K]
+hipError_t launch_lay(const StrRec *strs, const TailRec *trec, int64_t s0, int64_t s1, int64_t blob_bytes, int64_t N,
+                      const LayTables &o, int32_t *kid_cnt, int32_t *kid_parent, int32_t *kid_rank, int32_t *err,
+                      hipStream_t s);
+// after the last group: the entries of the other children, K at most
+hipError_t launch_kids(const StrRec *strs, int64_t K, int64_t N, Walk *walk, Kid *kid, const int32_t *kid_cnt,
+                       const int32_t *kid_parent, const int32_t *kid_rank, int32_t *kid_total, int32_t *err,
+                       hipStream_t s);
+// the heads of V tokens
+hipError_t launch_tok_heads(const uint32_t *tok_off, const uint8_t *tok_blob, int64_t V, TokHead *head, hipStream_t s);
 hipError_t launch_scan(const DevTables &t, hipStream_t s);
 hipError_t launch_zero(uint64_t *p, int64_t words, hipStream_t s);
 int64_t mark_blocks(int64_t N);
 hipError_t launch_fill_lists(const DevTables &t, hipStream_t s);
-// Tail compression's row_of and tail_span of the nodes the strings [s0, s1)
-// create, the roots' entries (root_rows: S (id, row) pairs; null: none) and
-// row_at over the blob positions [b0, b1) (after row_of of every node there).
-hipError_t launch_tail_tables(const StrRec *strs, const TailRec *trec, int64_t s0, int64_t s1,
-                              const int32_t *root_rows, int64_t S, const int32_t *node_at, int64_t b0, int64_t b1,
-                              int64_t N, int32_t *row_of, int32_t *tail_span, int32_t *row_at, int32_t *err,
-                              hipStream_t s);
 // nodes per block of the probe pass (its block b takes nodes [b * n, (b + 1) * n))
 int64_t probe_nodes_per_block();
 // tail compression without a table: the records of the listed hits (of
@@ -180,6 +176,7 @@ struct tam_vocab {
     void *arena = nullptr;
     const uint32_t *d_tok_off = nullptr;
     const uint8_t *d_tok_blob = nullptr;
+    const tam::TokHead *d_tok_head = nullptr;  // built on the device
     const uint16_t *d_fps = nullptr;
     const tam::SlotPay *d_pay = nullptr;
     const uint64_t *d_pay_hi = nullptr;
@@ -211,11 +208,10 @@ struct tam_handle {
     // tail compression (TAM_FLAG_TAIL_LISTS): see DevTables
     // row_of is kept on the host for the host API; tail_span and row_at only
     // for host-only handles.  A device compile lays all three out on the
-    // device from tail_rec and root_rows.
+    // device from tail_rec.
     tam::hvec<int32_t> tail_span, row_of, row_at;
     bool tails = false;                  // tail compression's split is kept
     tam::hvec<tam::TailRec> tail_rec;    // [K_unique] one per blob string
-    std::vector<int32_t> root_rows;      // [2 S] each set root's id and row_of
     int64_t dense_rows = 0;
     // tail compression without a table: the probe grid in the groups of nodes
     // the compile uploaded, each with its own buffer of records

@@ -217,6 +217,38 @@ def test_advance_stops_at_a_terminator(P):
         full_check(P, strings, vocab, flags=flags)
 
 
+@pytest.mark.parametrize("term", [0x22, 0x00, 0xff])
+def test_advance_at_window_edges(P, term):
+    """Every (node, token) advance for tokens around the 15 bytes of a token head
+    and the 63 bytes of a compare window, strings that branch at those offsets
+    and end there, and nodes with 63 to 66 and with 254 children."""
+    rng = np.random.default_rng(term)
+    T = bytes([term])
+    letters = [b"a", b"b", b"\x01"]
+    base = b"".join(letters[i] for i in rng.integers(0, 3, size=140))
+    strings = [base, b""]
+    for at in (0, 1, 2, 13, 14, 15, 16, 17, 30, 31, 61, 62, 63, 64, 65, 78, 79, 126, 127, 128):
+        strings += [base[:at] + b"c" + base[at:at + 70], base[:at] + b"cc", base[:at]]
+    for at, n in ((3, 63), (5, 64), (7, 65), (70, 66), (20, 254)):
+        strings += [base[:at] + bytes([c]) for c in range(256) if c != term][:n]
+    strings = list(dict.fromkeys(strings))
+    vocab = [bytes([c]) for c in range(256)] + [b""]
+    for n in (2, 3, 14, 15, 16, 17, 18, 31, 32, 62, 63, 64, 65, 66, 127, 128, 129):
+        for _ in range(6):
+            s = strings[int(rng.integers(0, len(strings)))] + T + b"\x00b"
+            at = int(rng.integers(0, max(1, len(s) - n + 1)))
+            t = s[at:at + n]
+            vocab += [t, t[:-1] + b"c", t + T]
+        vocab += [base[:n], base[:n] + b"c", base[:n] + T, base[1:n + 1]]
+    o = Oracle(strings, vocab, terminator=term)
+    h = P.compile(strings, vocab, terminator=term)
+    nodes = np.arange(-1, o.N + 1)
+    for t in range(len(vocab)):
+        tt = np.full(nodes.size, t)
+        assert np.array_equal(gpu_advance(h, nodes, tt), o.advance(nodes, tt)), vocab[t]
+    h.close()
+
+
 def test_tail_single_string(P):
     """One string: the whole trie is one path, so no node branches (the table
     keeps one unused row) and every row comes from a list."""
