@@ -21,8 +21,7 @@
 //               (canonical rows of handles without a dense table).
 // Serving (Section 2, Eq. 1 and the extended transition function):
 //   k_apply  -- write-mostly masking of [B, V] logits (lists and tail rows);
-//               k_apply_dense for dense-table rows, three rows per block (two
-//               for small batches); rows of any alignment.
+//               k_apply_dense for dense-table rows; rows of any alignment.
 //   k_advance-- B byte walks along the strings of the blob and over the
 //               children that leave them, one wave per row.
 //   k_export_dense, k_export_tail -- canonical rows out of the dense table and
@@ -52,9 +51,12 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWave = 64;
-constexpr int kApplyUnits = 1;       // 16-byte chunks per thread in k_apply (measured best)
-constexpr int kApplyRows = 3;        // rows per block of k_apply_dense (measured best on rows that change every call)
-constexpr int64_t kApplyMinBlocks = 4096;  // fewer blocks than this with kApplyRows: two rows per block
+// Apply: two chunks per thread while that leaves this many blocks (8 per CU, all
+// that run at once); with fewer, one per thread spreads a small batch further.
+// bf16 rows over V = 262,144 with tail compression, two against one: 1 row 3.4
+// and 3.1 us, 8 rows 3.9 and 3.7, 16 rows 4.2 and 4.1, 32 rows (2,048 blocks) 5.35
+// and 5.44, 256 rows 20.0 and 23.3 us.
+constexpr int64_t kApplyWide = 2048;
 // k_apply row sources: the valid lists, or with tail compression per row the
 // tail's hits or the branching node's dense row or list
 constexpr int kApplyLists = 1, kApplyTail = 2;
@@ -830,8 +832,9 @@ __device__ __forceinline__ uint32_t table_bits(const DevTables &t, int64_t trow,
 // One token id per lane (rel = id minus the first element of the block's span;
 // >= kSpan: none or outside): each thread sets the bits of its own chunks.  The
 // ids inside the span are few, so a ballot keeps only those.
-template <int E, int kSpan>
-__device__ __forceinline__ void take_ids(uint32_t rel, uint32_t (&bits)[kApplyUnits]) {
+template <int E, int U>
+__device__ __forceinline__ void take_ids(uint32_t rel, uint32_t (&bits)[U]) {
+    constexpr int kSpan = kBlock * U * E;
     uint64_t in_span = __ballot(rel < (uint32_t)kSpan);
     while (in_span) {
         const int j = __builtin_ctzll(in_span);
@@ -839,18 +842,19 @@ __device__ __forceinline__ void take_ids(uint32_t rel, uint32_t (&bits)[kApplyUn
         const uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)rel, j);
         const uint32_t lc = r / E;
 #pragma unroll
-        for (int u = 0; u < kApplyUnits; ++u)
+        for (int u = 0; u < U; ++u)
             if (lc == (uint32_t)(u * kBlock + threadIdx.x)) bits[u] |= 1u << (r % E);
     }
 }
 
 // The same for one id held by the whole wave.
-template <int E, int kSpan>
-__device__ __forceinline__ void set_id(uint32_t rel, uint32_t (&bits)[kApplyUnits]) {
+template <int E, int U>
+__device__ __forceinline__ void set_id(uint32_t rel, uint32_t (&bits)[U]) {
+    constexpr int kSpan = kBlock * U * E;
     if (rel >= (uint32_t)kSpan) return;
     const uint32_t lc = rel / E;
 #pragma unroll
-    for (int u = 0; u < kApplyUnits; ++u)
+    for (int u = 0; u < U; ++u)
         if (lc == (uint32_t)(u * kBlock + threadIdx.x)) bits[u] |= 1u << (rel % E);
 }
 
@@ -877,40 +881,68 @@ __device__ __forceinline__ void mask_partial(T *row, int64_t e0, int64_t V, uint
         if (!((bu >> i) & 1u)) row[e0 + i] = NegInf<T>::bits;
 }
 
+template <typename T>
+__device__ __forceinline__ uint32_t neg_word() {
+    return sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
+}
+
+// A chunk with -inf in place of the elements whose bit in bu is 0.
+template <typename T>
+__device__ __forceinline__ u32x4 merge_chunk(u32x4 x, uint32_t bu) {
+    u32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (sizeof(T) == 2) {
+            const uint32_t two = bu >> (2 * i);
+            const uint32_t keep = ((two & 1u) ? 0x0000ffffu : 0u) | ((two & 2u) ? 0xffff0000u : 0u);
+            o[i] = (x[i] & keep) | (0xFF80FF80u & ~keep);
+        } else {
+            o[i] = (bu >> i) & 1u ? x[i] : 0xFF800000u;
+        }
+    }
+    return o;
+}
+
 // Chunk [e0, e0 + E) lies inside the row.
 template <bool kAligned, int E>
 __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
     return (kAligned || e0 >= 0) && e0 + E <= V;
 }
 
-// List and tail rows.  Grid: x = groups of kBlock*kApplyUnits chunks of one row,
-// y = batch row.
-// Thread i of a block owns chunks c0 + u*kBlock + i, so every store instruction
-// covers 4 KiB per block contiguously (one chunk per thread writes fastest, as
-// for the table's zero fill).  All mask bits of the thread are read before its
-// first store.
-// Write-mostly: a chunk without a valid token gets one non-temporal -inf store
-// and no read; a fully valid chunk is skipped; a mixed chunk gets -inf stores
-// into its invalid elements only.  The bits of the block's span come from the
+// List and tail rows.  Grid: x = groups of kBlock*U chunks of one row, y = batch
+// row.  Thread i of a block owns chunks c0 + u*kBlock + i, so every store
+// instruction covers 4 KiB per block contiguously.  A block's life is the
+// dependent loads in front of its stores (node id; row_of with the tail's hits,
+// or list bounds, then ids), 1.3 us at which the chip's waves with one 16-byte
+// store per thread just reach the memory's rate: one more dependent load in
+// front cost 10% of a step.  Two chunks per thread for tail compression took
+// 28.2 -> 25.1 us per decode step of 256 bf16 rows over V = 262,144 (fill of the
+// same bytes alone: 21.2), over a forest 30.2 -> 26.9; three 27.2, four 27.2 us.
+// Plain lists are at the memory's rate with one (25.5 against 26.6 us with two).
+// Write-mostly: a chunk without a valid token is written and not read; a fully
+// valid chunk is skipped; a mixed chunk is read and merged, and stored by the same
+// instruction as the empty ones, so that a 128-byte line holding both is written
+// whole (-inf stores into its invalid elements only, without the read, wrote such
+// lines in parts: 10,000 word strings from the root 32.0 -> 30.5 us per step, a
+// forest 26.9 -> 26.6).  The bits of the block's span come from the
 // node's valid list (a ballot over a short list, an LDS bitmap for a long one),
 // from the tail's hits, or (kApplyTail) from the dense row of a branching node.
 // kAligned: every row's base is 16-byte aligned (no shift; computing it all the
 // same costs 1-2% of a forest's or a code list's decode step, as does unrolling
 // mask_partial).
-template <typename T, int kMode, bool kAligned>
+template <typename T, int kMode, int U, bool kAligned>
 __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__restrict__ node_ids,
                                                   T *__restrict__ logits, int64_t stride) {
     constexpr int E = 16 / (int)sizeof(T);
     constexpr uint32_t FULL = (1u << E) - 1u;
-    constexpr T NEG = NegInf<T>::bits;
-    constexpr int kSpan = kBlock * kApplyUnits * E;  // elements per block
+    constexpr int kSpan = kBlock * U * E;  // elements per block
     __shared__ uint32_t bm[kSpan / 32];
 
     const int64_t V = t.V;
     const int64_t b = blockIdx.y;
     const int32_t n = node_ids[b];
     const bool live = n >= 0 && (int64_t)n < t.N;
-    const int64_t c0 = (int64_t)blockIdx.x * kBlock * kApplyUnits;
+    const int64_t c0 = (int64_t)blockIdx.x * kBlock * U;
     T *row = logits + b * stride;
     const int a = kAligned ? 0 : row_shift(row);
     const int64_t nchunks = (V + a + E - 1) / E;
@@ -929,16 +961,16 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
     // lists: every row; tail compression without a table: the branching rows
     const bool use_list = kMode == kApplyLists || (kMode == kApplyTail && !tail_row && t.table == nullptr);
 
-    uint32_t bits[kApplyUnits];
+    uint32_t bits[U];
 #pragma unroll
-    for (int u = 0; u < kApplyUnits; ++u) bits[u] = 0;
+    for (int u = 0; u < U; ++u) bits[u] = 0;
     const uint32_t lo = (uint32_t)(c0 * E - a);  // first element of the span (wraps below 0 in the first one)
     if (tail_row) {
         // lane d-1 takes the token of length d starting below the tail (the
         // path below a tail has consecutive ids, so all of them were loaded)
         const int Lt = min(min(-1 - (int)trow, kWin), (int)t.max_len);
         const int32_t x = lane < Lt ? x_tail : -1;
-        take_ids<E, kSpan>(x >= 0 ? (uint32_t)x - lo : 0xffffffffu, bits);
+        take_ids<E, U>(x >= 0 ? (uint32_t)x - lo : 0xffffffffu, bits);
         // strings with several token ids (rare): walk their id chains
         uint64_t multi = __ballot(x <= -2);
         while (multi) {
@@ -947,7 +979,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
             const SlotPay pm = t.pay[-2 - __builtin_amdgcn_readlane(x, j)];
             int32_t v = pm.first;
             for (int k = 0; k < (int)pm.count; ++k) {
-                set_id<E, kSpan>((uint32_t)v - lo, bits);
+                set_id<E, U>((uint32_t)v - lo, bits);
                 v = t.dup_next[v];
             }
         }
@@ -955,7 +987,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
             const int32_t e0 = t.row_ptr[n], e1 = t.row_ptr[n + 1];
             for (int32_t k0 = e0; k0 < e1; k0 += kWave) {
                 const uint32_t rel = k0 + lane < e1 ? (uint32_t)t.entries[k0 + lane] - lo : 0xffffffffu;
-                take_ids<E, kSpan>(rel, bits);
+                take_ids<E, U>(rel, bits);
             }
         }
     } else if (use_list) {
@@ -964,7 +996,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
             // short list (block-uniform branch): every wave reads the ids into its
             // lanes, keeps those inside the block's span (a ballot), and each thread
             // picks the bits of its own chunks from the few that remain
-            take_ids<E, kSpan>(lane < e1 - e0 ? (uint32_t)t.entries[e0 + lane] - lo : 0xffffffffu, bits);
+            take_ids<E, U>(lane < e1 - e0 ? (uint32_t)t.entries[e0 + lane] - lo : 0xffffffffu, bits);
         } else {
             // long list: scatter through an LDS bitmap of the block's span
             for (int i = threadIdx.x; i < kSpan / 32; i += kBlock) bm[i] = 0;
@@ -975,21 +1007,21 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
             }
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < kApplyUnits; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const uint32_t bit = (uint32_t)((u * kBlock + threadIdx.x) * E);
                 bits[u] = (bm[bit >> 5] >> (bit & 31)) & FULL;
             }
         }
     } else if (trow >= 0) {
 #pragma unroll
-        for (int u = 0; u < kApplyUnits; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int64_t c = c0 + u * kBlock + threadIdx.x;
             if (c < nchunks) bits[u] = table_bits<E>(t, trow, c, a);
         }
     }
 
 #pragma unroll
-    for (int u = 0; u < kApplyUnits; ++u) {
+    for (int u = 0; u < U; ++u) {
         const int64_t c = c0 + u * kBlock + threadIdx.x;
         if (c >= nchunks) break;
         const uint32_t bu = bits[u];
@@ -997,102 +1029,67 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
         const int64_t e0 = c * E - a;
         if (whole_chunk<kAligned, E>(e0, V)) {
             u32x4 *p = reinterpret_cast<u32x4 *>(row + e0);
-            if (bu == 0) {
-                const uint32_t w = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
-                __builtin_nontemporal_store(u32x4{w, w, w, w}, p);
-            } else if (use_list || tail_row) {
-                // mixed, list or tail row: -inf into the invalid elements only, no
-                // read (the memory side merges the partial lines; measured faster
-                // for short valid lists)
-                uint32_t *q = reinterpret_cast<uint32_t *>(p);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (sizeof(T) == 2) {
-                        const uint32_t two = (bu >> (2 * i)) & 3u;
-                        if (two == 0)
-                            q[i] = 0xFF80FF80u;
-                        else if (two == 1)
-                            row[e0 + 2 * i + 1] = NEG;
-                        else if (two == 2)
-                            row[e0 + 2 * i] = NEG;
-                    } else if (!((bu >> i) & 1u)) {
-                        q[i] = 0xFF800000u;
-                    }
-                }
-            } else {
-                // mixed, dense table: read, merge, write the whole chunk (measured
-                // faster where valid tokens are spread over many chunks)
-                u32x4 x = *p;
-                T vals[E];
-                __builtin_memcpy(vals, &x, 16);
-#pragma unroll
-                for (int i = 0; i < E; ++i)
-                    if (!((bu >> i) & 1u)) vals[i] = NEG;
-                __builtin_memcpy(&x, vals, 16);
-                *p = x;
-            }
+            const uint32_t w = neg_word<T>();
+            u32x4 o{w, w, w, w};
+            if (bu != 0) o = merge_chunk<T>(*p, bu);
+            __builtin_nontemporal_store(o, p);
         } else {
             mask_partial<T, kAligned>(row, e0, V, bu);
         }
     }
 }
 
-// Dense-table rows, kApplyRows rows per block: block (x, y) takes span x (one
-// chunk per thread) of the adjacent rows R y .. R y + R - 1.  All the rows'
-// mask bytes are loaded first, then the logits of their mixed chunks, then the
-// stores: a block keeps kApplyRows mask loads in flight, while at any moment
-// the blocks still write a few compact windows of the logits.  Write-mostly as
-// in k_apply (non-temporal -inf stores, read-merge-write of mixed chunks, also
-// stored non-temporally).  kAligned: every row's base is 16-byte aligned, so the
-// rows' chunks share their elements and no shift is computed.
-template <typename T, int R, bool kAligned>
+// Dense-table rows: block (x, y) takes chunks x * kBlock * U .. of row y, U per
+// thread.  The mask bytes are loaded first, then the logits of the mixed chunks,
+// then everything is stored, the merged chunks and the empty ones in one
+// instruction: a 128-byte line of both is then written whole, where two stores
+// in the two arms of a branch wrote it in two parts (256 bf16 rows decoding over
+// V = 151,936: 28.0 -> 27.6 us per step; anywhere in a table of V = 262,144 rows:
+// 28.2 -> 27.5 us).
+// A block's life is the dependent loads in front of its stores (node id, mask
+// byte, logits), so it is worth two chunks per thread once the batch fills the
+// chip (kApplyWide): the former three rows of one chunk each kept as many
+// loads in flight but swept three windows of the logits at once (28.4 us per
+// step, 3.1 against 2.9 TB/s over a decode from the root); three chunks take 30.0,
+// four 31.5 us per step.
+// kAligned: every row's base is 16-byte aligned (no shift).
+template <typename T, int U, bool kAligned>
 __global__ void __launch_bounds__(kBlock) k_apply_dense(DevTables t, const int32_t *__restrict__ node_ids,
-                                                        int64_t rows, T *__restrict__ logits, int64_t stride) {
+                                                        T *__restrict__ logits, int64_t stride) {
     constexpr int E = 16 / (int)sizeof(T);
     constexpr uint32_t FULL = (1u << E) - 1u;
-    constexpr T NEG = NegInf<T>::bits;
     const int64_t V = t.V;
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int a[R];
-    bool in[R];  // the row exists and has a chunk c
-    uint32_t bits[R];
+    const int64_t b = blockIdx.y;
+    const int64_t c0 = (int64_t)blockIdx.x * kBlock * U + threadIdx.x;
+    T *row = logits + b * stride;
+    const int a = kAligned ? 0 : row_shift(row);
+    const int64_t nchunks = (V + a + E - 1) / E;
+    const int32_t n = node_ids[b];
+    const bool live = n >= 0 && (int64_t)n < t.N;
+    uint32_t bits[U];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t b = (int64_t)blockIdx.y * R + r;
-        a[r] = kAligned ? 0 : row_shift(logits + b * stride);
-        in[r] = b < rows && c < (V + a[r] + E - 1) / E;
-        const int32_t n = b < rows ? node_ids[b] : -1;
-        bits[r] = 0;  // a dead row: every token invalid
-        if (n >= 0 && (int64_t)n < t.N && in[r]) bits[r] = table_bits<E>(t, n, c, a[r]);
+    for (int u = 0; u < U; ++u) {
+        const int64_t c = c0 + u * kBlock;
+        bits[u] = 0;  // a dead row: every token invalid
+        if (live && c < nchunks) bits[u] = table_bits<E>(t, n, c, a);
     }
-    u32x4 xv[R];
+    u32x4 xv[U];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t b = (int64_t)blockIdx.y * R + r, e0 = c * E - a[r];
-        if (in[r] && whole_chunk<kAligned, E>(e0, V) && bits[r] != 0 && bits[r] != FULL)
-            xv[r] = *reinterpret_cast<const u32x4 *>(logits + b * stride + e0);
+    for (int u = 0; u < U; ++u) {
+        const int64_t c = c0 + u * kBlock, e0 = c * E - a;
+        if (c < nchunks && whole_chunk<kAligned, E>(e0, V) && bits[u] != 0 && bits[u] != FULL)
+            xv[u] = *reinterpret_cast<const u32x4 *>(row + e0);
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t b = (int64_t)blockIdx.y * R + r, e0 = c * E - a[r];
-        const uint32_t bu = bits[r];
-        if (!in[r] || bu == FULL) continue;
-        T *row = logits + b * stride;
+    for (int u = 0; u < U; ++u) {
+        const int64_t c = c0 + u * kBlock, e0 = c * E - a;
+        const uint32_t bu = bits[u];
+        if (c >= nchunks || bu == FULL) continue;
         if (whole_chunk<kAligned, E>(e0, V)) {
-            u32x4 *p = reinterpret_cast<u32x4 *>(row + e0);
-            if (bu == 0) {
-                const uint32_t w = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
-                __builtin_nontemporal_store(u32x4{w, w, w, w}, p);
-            } else {
-                T vals[E];
-                __builtin_memcpy(vals, &xv[r], 16);
-#pragma unroll
-                for (int i = 0; i < E; ++i)
-                    if (!((bu >> i) & 1u)) vals[i] = NEG;
-                u32x4 o;
-                __builtin_memcpy(&o, vals, 16);
-                __builtin_nontemporal_store(o, p);
-            }
+            const uint32_t w = neg_word<T>();
+            u32x4 o{w, w, w, w};
+            if (bu != 0) o = merge_chunk<T>(xv[u], bu);
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(row + e0));
         } else {
             mask_partial<T, kAligned>(row, e0, V, bu);
         }
@@ -2061,68 +2058,50 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
     return hipGetLastError();
 }
 
-// Dense-table rows, R rows per block; grid.y (row groups) is limited to 65535
-// per launch.
-template <int R, bool kAligned>
-static hipError_t launch_apply_dense(const DevTables &t, const int32_t *node_ids, int64_t B, void *logits, int dtype,
-                                     int64_t row_stride, int64_t gx1, hipStream_t s) {
-    for (int64_t r0 = 0; r0 < B; r0 += (int64_t)65535 * R) {
-        const int64_t rows = std::min<int64_t>(B - r0, (int64_t)65535 * R);
-        const dim3 grid((unsigned)gx1, (unsigned)grid_for(rows, R));
-        if (dtype == TAM_DTYPE_BF16)
-            hipLaunchKernelGGL((k_apply_dense<uint16_t, R, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, rows,
-                               static_cast<uint16_t *>(logits) + r0 * row_stride, row_stride);
+// U chunks per thread; grid.y is limited to 65535 rows per launch.
+template <typename T, int U, bool kAligned>
+static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, T *logits,
+                                    int64_t row_stride, int64_t nchunks, hipStream_t s) {
+    for (int64_t r0 = 0; r0 < B; r0 += 65535) {
+        const dim3 grid(grid_for(nchunks, kBlock * U), (unsigned)std::min<int64_t>(B - r0, 65535));
+        T *p = logits + r0 * row_stride;
+        if (t.row_of)
+            hipLaunchKernelGGL((k_apply<T, kApplyTail, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
+                               row_stride);
+        else if (t.table)
+            hipLaunchKernelGGL((k_apply_dense<T, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
+                               row_stride);
         else
-            hipLaunchKernelGGL((k_apply_dense<uint32_t, R, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, rows,
-                               static_cast<uint32_t *>(logits) + r0 * row_stride, row_stride);
+            hipLaunchKernelGGL((k_apply<T, kApplyLists, 1, kAligned>),
+                               dim3(grid_for(nchunks, kBlock), grid.y), dim3(kBlock), 0, s, t, node_ids + r0, p,
+                               row_stride);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-// List and tail rows; grid.y is limited to 65535 rows per launch.
-template <typename T, bool kAligned>
-static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, void *logits,
-                                    int64_t row_stride, unsigned gx, hipStream_t s) {
-    for (int64_t r0 = 0; r0 < B; r0 += 65535) {
-        const dim3 grid(gx, (unsigned)std::min<int64_t>(B - r0, 65535));
-        T *p = static_cast<T *>(logits) + r0 * row_stride;
-        if (t.row_of)
-            hipLaunchKernelGGL((k_apply<T, kApplyTail, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
-                               row_stride);
-        else
-            hipLaunchKernelGGL((k_apply<T, kApplyLists, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
-                               row_stride);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+template <typename T>
+static hipError_t launch_apply_typed(const DevTables &t, const int32_t *node_ids, int64_t B, T *logits,
+                                     int64_t row_stride, hipStream_t s) {
+    constexpr int E = 16 / (int)sizeof(T);
+    const bool aligned =
+        (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && ((row_stride * (int64_t)sizeof(T)) & 15) == 0;
+    const int64_t nchunks = (t.V + (aligned ? 0 : E - 1) + E - 1) / E;  // a shifted row may touch one more
+    // two chunks per thread while that leaves kApplyWide blocks
+    const bool wide = (int64_t)grid_for(nchunks, 2 * kBlock) * B >= kApplyWide;
+    if (aligned)
+        return wide ? launch_apply_rows<T, 2, true>(t, node_ids, B, logits, row_stride, nchunks, s)
+                    : launch_apply_rows<T, 1, true>(t, node_ids, B, logits, row_stride, nchunks, s);
+    return wide ? launch_apply_rows<T, 2, false>(t, node_ids, B, logits, row_stride, nchunks, s)
+                : launch_apply_rows<T, 1, false>(t, node_ids, B, logits, row_stride, nchunks, s);
 }
 
 hipError_t launch_apply(const DevTables &t, const int32_t *node_ids, int64_t B, void *logits, int dtype,
                         int64_t row_stride, hipStream_t s) {
-    const int E = dtype == TAM_DTYPE_BF16 ? 8 : 4;
-    const int elem = dtype == TAM_DTYPE_BF16 ? 2 : 4;
-    const bool aligned = (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && ((row_stride * elem) & 15) == 0;
-    const int64_t nchunks = (t.V + (aligned ? 0 : E - 1) + E - 1) / E;  // a shifted row may touch one more
-    if (!t.row_of && t.table) {
-        const int64_t gx1 = grid_for(nchunks, kBlock);
-        // three rows per block while that keeps 16 blocks per CU in flight,
-        // else two (64 fp32 rows over V = 128,256: 8.2 against 8.9 µs per call)
-        const bool three = gx1 * ((B + kApplyRows - 1) / kApplyRows) >= kApplyMinBlocks;
-        if (aligned)
-            return three ? launch_apply_dense<kApplyRows, true>(t, node_ids, B, logits, dtype, row_stride, gx1, s)
-                         : launch_apply_dense<2, true>(t, node_ids, B, logits, dtype, row_stride, gx1, s);
-        return three ? launch_apply_dense<kApplyRows, false>(t, node_ids, B, logits, dtype, row_stride, gx1, s)
-                     : launch_apply_dense<2, false>(t, node_ids, B, logits, dtype, row_stride, gx1, s);
-    }
-    const unsigned gx = grid_for(nchunks, kBlock * kApplyUnits);
     if (dtype == TAM_DTYPE_BF16)
-        return aligned ? launch_apply_rows<uint16_t, true>(t, node_ids, B, logits, row_stride, gx, s)
-                       : launch_apply_rows<uint16_t, false>(t, node_ids, B, logits, row_stride, gx, s);
-    return aligned ? launch_apply_rows<uint32_t, true>(t, node_ids, B, logits, row_stride, gx, s)
-                   : launch_apply_rows<uint32_t, false>(t, node_ids, B, logits, row_stride, gx, s);
+        return launch_apply_typed(t, node_ids, B, static_cast<uint16_t *>(logits), row_stride, s);
+    return launch_apply_typed(t, node_ids, B, static_cast<uint32_t *>(logits), row_stride, s);
 }
 
 hipError_t launch_advance(const DevTables &t, const int32_t *node_ids, const int32_t *token_ids, int64_t B,

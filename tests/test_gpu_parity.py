@@ -1076,6 +1076,30 @@ def test_apply_rows_at_every_alignment(P, flags, V):
                 assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, off, pad)
 
 
+@pytest.mark.parametrize("flags", FLAGS, ids=FLAG_IDS)
+@pytest.mark.parametrize("V", [4088, 4095, 4096, 4097, 4104, 6145])
+def test_apply_two_chunks_per_thread(P, flags, V):
+    """Batches large enough for two chunks per thread, V at the edges of a
+    block's span, aligned rows and rows 1 and 3 elements off."""
+    w = W.config(1)
+    vocab = (w.vocab[97:123] + w.vocab[:97] + w.vocab[123:])[:V]
+    o = Oracle(w.strings, vocab)
+    h = P.compile(w.strings, vocab, flags=flags)
+    B = 2100
+    nodes = np.random.default_rng(V).integers(-1, o.N + 1, size=B).astype(np.int32)
+    nodes[:64] = 0
+    ids = torch.as_tensor(nodes, device="cuda")
+    for dtype, off, stride in (("fp32", 0, V + (-V) % 4), ("fp32", 1, V), ("bf16", 0, V + (-V) % 8), ("bf16", 3, V)):
+        np_t = np.uint16 if dtype == "bf16" else np.uint32
+        x = host_logits(1, off + B * stride + 8, dtype, seed=off)
+        dev = x.cuda()
+        h.apply_mask(ids, dev[0, off:off + B * stride].view(B, stride)[:, :V])
+        exp = bits_of(x).view(np_t).copy()
+        inner = exp[0, off:off + B * stride].reshape(B, stride)
+        inner[:, :V] = o.apply(nodes, np.ascontiguousarray(inner[:, :V]), 1 if dtype == "bf16" else 0)
+        assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, off)
+
+
 def test_many_rows_grid_split(P):
     """More than 65,535 batch rows in one call (the launcher splits the grid)."""
     strings = [b"ab", b"b"]
