@@ -14,7 +14,7 @@ the C ABI's CSR form (packing a Python list into it is timed on its own).
 
 The same line also reports the workload under tail compression
 (TAM_FLAG_TAIL_LISTS: dense rows only for branching nodes, tails read back from
-the probe's hits), which gives bit-identical masks from a much smaller table,
+the probe pass), which gives bit-identical masks from a much smaller table,
 and with rows built on demand (TAM_FLAG_LAZY_ROWS: no mask at compile, a row
 cache filled by the decode steps).
 
@@ -499,11 +499,10 @@ class Bench:
         apply_graph_us = self.graph_us(apply_next, 100)
 
         # the compile kernels, each with its algorithmic bytes: the zero fill
-        # writes the dense rows; the probe pass writes the hits, 4 bytes per node
-        # and suffix length <= 16 (they hold the tails' masks and feed the
+        # writes the dense rows; the probe pass writes 8 bytes per node (which
+        # tokens are suffixes of its path: they hold the tails' masks and feed the
         # lists); the lists' prefix sum and fill write row offsets and entries
-        lw = np.minimum(np.minimum(h.depth, h.max_token_len), 16)
-        hit_bytes = 4 * int(lw.sum())
+        hit_bytes = 8 * h.num_nodes
         sha = kernels_sha()
         kernels = {}
         if "zero" in alone and h.dense_rows:

@@ -70,11 +70,76 @@ struct alignas(16) SlotPay {
 // pay_hi[string]: byte k - 8 = token byte len-1-k for 8 <= k < min(len, 16),
 // then zeros (0 for strings of at most 8 bytes).
 
-// What the probe pass stores per (node, suffix length): the token id when the
-// string has one id, -2 - its string number when it has several, -1 when no
-// token matches.
+// A hit of a token string: the token id when the string has one id, -2 - its
+// string number when it has several, -1 when no token matches.
 __host__ __device__ __forceinline__ int32_t hit_of_slot(int32_t slot, int32_t first, int count) {
     return count == 1 ? first : -2 - slot;
+}
+
+// ---------------------------------------------------------------------------
+// Suffix table: for a path's last min(depth, 16) bytes, all token strings that
+// are suffixes of it, found from the longest one alone.
+//
+// The longest is found by a binary search over its length (kShortLen + 1 .. kWin,
+// four probes), which needs every token to be announced at the shorter lengths
+// the search passes on its way to it: a token of length d also enters its suffix
+// of each such length (a marker).  This is the binary search on prefix lengths
+// of Waldvogel, Varghese, Turner and Plattner (1997), turned to suffixes.  An entry
+// (token or marker) knows the token strings that are suffixes of it: a bit per
+// length, and their hits in ascending length.  A marker's are the first of its
+// token's, so both point into the token's list.
+//
+// Entries lie in buckets of eight 15-bit fingerprints (0: empty), one 16-byte load
+// each: slot s in the low (s < 4) or high half of word s & 3; the top bit of slot
+// 7's half says that a key that belongs here had to move to the next bucket.
+// Entry 8 * bucket + slot has its payload there, read once per search: the
+// buckets hold nothing else, so that the four probes of a search stay within
+// 3 bytes per token and marker (about 1.5 MB for a vocabulary of 262,144), which
+// the L2 of every XCD holds beside what streams through it.
+// ---------------------------------------------------------------------------
+constexpr int kSufSlots = 8;
+constexpr uint32_t kSufOver = 0x80000000u;  // of word 3
+
+__host__ __device__ __forceinline__ uint32_t suf_fingerprint(uint64_t key) {
+    const uint32_t f = (uint32_t)(key >> 49);  // 15 bits; 0 marks an empty slot
+    return f ? f : 1u;
+}
+
+__host__ __device__ __forceinline__ uint32_t suf_home(uint64_t key, uint32_t buckets) {
+    return (uint32_t)(((uint64_t)(uint32_t)key * buckets) >> 32);
+}
+
+struct alignas(16) SufPay {
+    uint64_t lo, hi;    // the entry's bytes, last first, then zeros
+    uint32_t off;       // its list in suf_ids
+    uint16_t mask, len; // bit d - 1: a token string of length d is a suffix; the entry's length
+    int32_t total;      // token ids of those strings
+    int32_t unused;
+};
+// The same for a path's last one or two bytes (short_index), without a token
+// longer than that.
+struct alignas(16) SufRef {
+    uint32_t off, mask;
+    int32_t total, unused;
+};
+// What the probe pass keeps per node.
+struct alignas(8) NodeSuf {
+    uint32_t off, mask;
+};
+
+// The lengths the search for a token of length d (kShortLen < d <= kWin) visits,
+// d last, into at[4]; returns how many.
+__host__ __device__ __forceinline__ int suf_path(int d, int (&at)[4]) {
+    int lo = kShortLen, hi = kWin + 1, n = 0;
+    for (;;) {
+        const int mid = (lo + hi) / 2;
+        if (mid <= d) at[n++] = mid;
+        if (mid == d) return n;
+        if (mid < d)
+            lo = mid;
+        else
+            hi = mid;
+    }
 }
 
 // One string of the trie's blob, in blob order; the device lays out node_at
@@ -151,10 +216,14 @@ struct DevTables {
     const SlotPay *pay;         // [slot_mask+1]
     const uint64_t *pay_hi;     // [slot_mask+1] bytes 8..15 of the reversed token
     const int32_t *short_hits;  // [kShortEntries] hit_of_slot of every string of <= kShortLen bytes, or -1
+    const uint32_t *suf_fps;    // [4 * suf_buckets] the suffix table's buckets
+    const SufPay *suf_pay;      // [8 * suf_buckets]
+    const SufRef *suf_short;    // [kShortEntries]
+    const int32_t *suf_ids;     // the lists: hits in ascending length
     const int32_t *dup_next;    // [V] next id with the same bytes, -1 at the end
     const uint8_t *len_present; // [max_len+1] 1 if some token has that length
     // valid lists (a4) and dense table
-    int32_t *hits;              // [kWin][N] hit_of_slot of the suffix of length d+1 of node m, or -1
+    NodeSuf *node_suf;          // [N] the token strings that are suffixes of the node's path (<= kWin bytes)
     int32_t *count;             // [N]
     int32_t *row_ptr;           // [N+1]
     int32_t *cursor;            // [N]
@@ -184,6 +253,7 @@ struct DevTables {
                                 // to the lists, with the tails' tokens longer than kWin
     int64_t blob_bytes;
     uint64_t slot_mask;         // slots - 1 (slots = a power of two, >= kBucket)
+    uint32_t suf_buckets;
     uint64_t len_mask;          // bit d (d < 64): some token has length d
     int32_t max_len;
     int32_t terminator;

@@ -455,18 +455,32 @@ tam_status build_vocab(const uint8_t *tb, const int64_t *to, int64_t V, tam_voca
     if (total > 0) std::memcpy(h->tok_blob.data(), tb + to[0], (size_t)total);
     std::memset(h->tok_blob.data() + total, 0, (size_t)kBlobPad);
     const int64_t chunk = 1 << 14, nchunks = (V + chunk - 1) / chunk;
-    std::vector<int64_t> cmax((size_t)nchunks, 0);
+    std::vector<int64_t> cmax((size_t)nchunks, 0), cent((size_t)nchunks, 0), cids((size_t)nchunks, 0);
+    int64_t suf_steps[kWin + 1] = {};  // entries a token of that length makes in the suffix table
+    for (int d = kShortLen + 1; d <= kWin; ++d) {
+        int at[4];
+        suf_steps[d] = suf_path(d, at);
+    }
     parallel_for(nchunks, host_threads(nchunks), [&](int64_t c) {
-        int64_t m = 0;
+        int64_t m = 0, ent = 0, ids = 0;
         for (int64_t v = c * chunk; v < std::min(V, (c + 1) * chunk); ++v) {
             h->tok_off[(size_t)v] = (uint32_t)(to[v] - to[0]);
-            m = std::max<int64_t>(m, to[v + 1] - to[v]);
+            const int64_t len = to[v + 1] - to[v];
+            m = std::max<int64_t>(m, len);
+            if (len <= kWin) {
+                ent += suf_steps[len];
+                ids += len;
+            }
         }
         cmax[(size_t)c] = m;
+        cent[(size_t)c] = ent;
+        cids[(size_t)c] = ids;
     });
     h->tok_off[(size_t)V] = (uint32_t)(to[V] - to[0]);
     int64_t max_len = 0;
     for (int64_t m : cmax) max_len = std::max(max_len, m);
+    for (int64_t e : cent) h->suf.entries += e;
+    for (int64_t i : cids) h->suf.ids += i;
     if (max_len > 65535) {
         *err = "a token is longer than 65535 bytes";
         return TAM_E_TOOLARGE;

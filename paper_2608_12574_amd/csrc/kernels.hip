@@ -2,18 +2,18 @@
 //
 // Mask compile (Section 4.1, valid[n] for every trie node n):
 //   k_zero   -- zero fill of the dense table (pure streaming stores).
-//   k_probe  -- two lanes per non-root node m (in different waves), seven
-//               hashed suffix lengths each: the last d <= min(depth(m), ℓ)
-//               bytes of prefix(m) are hashed (read backwards from a 16-byte
-//               register window) and looked up in the vocabulary table; a hit of
-//               token t at d = |t| means t is valid at the ancestor d levels up,
-//               because t's walk from there ends at m.  This is the paper's
-//               crediting of a match to the node |t| bytes back (Section 4.2),
-//               done for all nodes at once instead of along a DFS.  It keeps
-//               the hits, ORs them into the zeroed table with 64-bit atomics
-//               (nodes with a dense row) and, for lists, counts per node
-//               (without a table under tail compression, it also records
-//               each hit listed on a branching node with its rank).
+//   k_probe  -- one lane per non-root node m: the token strings that are suffixes
+//               of prefix(m) are found from the longest one (a binary search over
+//               its length in the vocabulary's suffix table); a token t of length
+//               d = |t| among them is valid at the ancestor d levels up, because
+//               t's walk from there ends at m.  This is the paper's crediting of a
+//               match to the node |t| bytes back (Section 4.2), done for all nodes
+//               at once instead of along a DFS.  It keeps which they are per
+//               node, ORs them into the zeroed table with 64-bit atomics (nodes
+//               with a dense row) and, for lists, counts per node (without a table
+//               under tail compression, it also records each hit listed on a
+//               branching node with its rank).
+//   k_suf_*  -- the suffix table, once per vocabulary.
 //   k_scan_* -- exclusive prefix sum of the counts into row offsets.
 //   k_fill   -- writes the hits' token ids into the per-node lists;
 //               k_fill_records places the recorded hits instead.
@@ -247,17 +247,14 @@ __device__ __forceinline__ int32_t probe(const DevTables &t, uint64_t key, int d
     return probe_from(t, home_bucket(t, key), fingerprint(key), d, lo, hi, pos, pay);
 }
 
-// A node's suffix lengths are split over kProbeLanes lanes: lane g hashes the
-// lengths kShortLen + 1 + g * kLaneLens .. kShortLen + (g + 1) * kLaneLens,
-// lane 0 also reads the short ones.
-constexpr int kProbeLanes = 2;
-constexpr int kLaneLens = (kWin - kShortLen) / kProbeLanes;
-static_assert(kLaneLens * kProbeLanes == kWin - kShortLen, "lengths split evenly over the lanes");
+// The hashed lengths are probed in two halves of kLaneLens.
+constexpr int kLaneLens = (kWin - kShortLen) / 2;
+static_assert(kLaneLens * 2 == kWin - kShortLen, "lengths split evenly");
 
 // The hits (hit_of_slot, or -1) of the suffixes of length d = kD0 + 1 ..
-// kD0 + kLaneLens (and, for lane 0, 1 .. kShortLen) of the path ending at
-// blob[pos], window (lo, hi); only d <= Lw <= kWin are probed.  hit[i] is the
-// hit of length kD0 + 1 + i (lane 0: hit[kLaneLens + d - 1] for the short d).
+// kD0 + kLaneLens (and, with the lower half, 1 .. kShortLen) of a window (lo,
+// hi); only d <= Lw <= kWin are probed.  hit[i] is the hit of length kD0 + 1 + i
+// (lower half: hit[kLaneLens + d - 1] for the short d).
 // The hash state advances one byte per length, and the lengths are unrolled,
 // so every byte extract and mask is a constant.  The home buckets of the
 // lane's lengths are loaded together, then the payload (and for lengths beyond
@@ -386,16 +383,168 @@ __device__ __forceinline__ int list_span(const DevTables &t, int64_t m) {
     return t.table ? 0 : INT_MAX;
 }
 
-// Probe pass: kProbeLanes lanes per node m, in different waves (lane g: the
-// suffix lengths of probe_lengths<kShortLen + g * kLaneLens>), all d <= min(depth, ℓ, 16) of
-// prefix(m).  The suffix of length d equal to token t means t is valid at the
-// ancestor d levels up, node_at[pos - d].  The hit (hit_of_slot: the token
-// id, or the slot of a string with several ids, or -1) goes to hits[d-1][m];
-// the tails of tail compression read their tokens back from there.  Longer
-// tokens are probed again where needed (long_hits, by the last lane).  All
-// loads of a lane's main path are issued before its first store or atomic
-// (loads, stores and atomics share one vector-memory counter here); the rare
-// lengths a home bucket does not settle follow, one at a time.
+// The bits of the lengths 1 .. d (of at most kWin).
+__device__ __forceinline__ uint32_t lengths_to(int d) {
+    return d >= kWin ? (1u << kWin) - 1u : d <= 0 ? 0u : (1u << d) - 1u;
+}
+
+// The hit of length k + 1 in the list of a mask with bit k set.
+__device__ __forceinline__ int32_t suf_hit(const DevTables &t, uint32_t off, uint32_t mask, int k) {
+    return t.suf_ids[off + __popc(mask & ((1u << k) - 1u))];
+}
+
+__device__ __forceinline__ u32x4 suf_bucket(const DevTables &t, uint32_t b) {
+    return reinterpret_cast<const u32x4 *>(t.suf_fps)[b];
+}
+
+// The first min(len, 16) reversed bytes of a window equal an entry's of length d.
+__device__ __forceinline__ bool suf_equal(const SufPay &p, int d, uint64_t lo, uint64_t hi) {
+    const uint64_t ml = d >= 8 ? ~0ull : ~0ull >> (64 - 8 * d);
+    const uint64_t mh = d >= 16 ? ~0ull : d <= 8 ? 0ull : ~0ull >> (64 - 8 * (d - 8));
+    return (int)p.len == d && (lo & ml) == p.lo && (hi & mh) == p.hi;
+}
+
+// Bits of the slots whose fingerprint is fp: slot s at bit (s & 3) + 16 * (s >> 2).
+__device__ __forceinline__ uint32_t suf_match(u32x4 q, uint32_t fp) {
+    const uint32_t fp2 = fp | (fp << 16);
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t x = (q[k] ^ fp2) & 0x7fff7fffu;
+        m |= (~(x + 0x7fff7fffu) & 0x80008000u) >> (15 - k);  // a half of x is 0
+    }
+    return m;
+}
+
+__device__ __forceinline__ int32_t suf_entry(uint32_t bucket, int bit) {
+    return (int32_t)(bucket * kSufSlots + (uint32_t)((bit & 3) | ((bit >> 4) << 2)));
+}
+
+// The number of the entry that equals the window's last d bytes, whose hash
+// state is h, or -1: every fingerprint match compared, on to the next bucket
+// while keys were moved there.
+__device__ __forceinline__ int32_t suf_find(const DevTables &t, uint32_t h, int d, uint64_t lo, uint64_t hi) {
+    const uint64_t key = hash_final(h);
+    const uint32_t fp = suf_fingerprint(key);
+    for (uint32_t b = suf_home(key, t.suf_buckets);; b = b + 1 == t.suf_buckets ? 0 : b + 1) {
+        const u32x4 q = suf_bucket(t, b);
+        for (uint32_t m = suf_match(q, fp); m; m &= m - 1) {
+            const int32_t n = suf_entry(b, __builtin_ctz(m));
+            if (suf_equal(t.suf_pay[n], d, lo, hi)) return n;
+        }
+        if (!(q.w & kSufOver)) return -1;
+    }
+}
+
+// The search with every step compared (suf_search's rare way out).
+__device__ __forceinline__ int32_t suf_search_exact(const DevTables &t, int Lw, uint64_t lo, uint64_t hi) {
+    int a = kShortLen, b = kWin + 1;
+    int32_t best = -1;
+    while (b - a > 1) {
+        const int mid = (a + b) / 2;
+        int32_t n = -1;
+        if (mid <= Lw) {
+            uint32_t h = kHashSeed;
+            for (int k = 0; k < mid; ++k) h = hash_step(h, window_byte(lo, hi, k));
+            n = suf_find(t, h, mid, lo, hi);
+        }
+        if (n >= 0) {
+            best = n;
+            a = mid;
+        } else {
+            b = mid;
+        }
+    }
+    return best;
+}
+
+// The token strings that are suffixes of the window's last Lw bytes (1 <= Lw <=
+// kWin).  Four dependent probes of one 16-byte load each, taken on the
+// fingerprint alone; only the last one that matched is compared: if it holds,
+// every shorter one on the way does (they are its token's markers), and a miss
+// needs no comparison.  A false match repeats the search with comparisons (1 node
+// in 5,000).
+__device__ __forceinline__ SufRef suf_search(const DevTables &t, int Lw, uint64_t lo, uint64_t hi) {
+    uint32_t hs[kWin + 1];
+    uint32_t h = kHashSeed;
+#pragma unroll
+    for (int k = 1; k <= kWin; ++k) {
+        h = hash_step(h, window_byte(lo, hi, k - 1));
+        hs[k] = h;
+    }
+    int32_t best = -1;
+    int best_d = 0;
+    auto look = [&](int d, uint32_t state) {
+        if (d > Lw) return false;
+        const uint64_t key = hash_final(state);
+        const uint32_t fp = suf_fingerprint(key);
+        uint32_t b = suf_home(key, t.suf_buckets);
+        u32x4 q = suf_bucket(t, b);
+        uint32_t m = suf_match(q, fp);
+        while (m == 0 && (q.w & kSufOver)) {  // keys moved on from here (1 bucket in 200)
+            b = b + 1 == t.suf_buckets ? 0 : b + 1;
+            q = suf_bucket(t, b);
+            m = suf_match(q, fp);
+        }
+        if (m == 0) return false;
+        best = suf_entry(b, __builtin_ctz(m));
+        best_d = d;
+        return true;
+    };
+    const bool p1 = look(9, hs[9]);
+    const bool p2 = look(p1 ? 13 : 5, p1 ? hs[13] : hs[5]);
+    const int d3 = p1 ? (p2 ? 15 : 11) : (p2 ? 7 : 3);
+    const bool p3 = look(d3, p1 ? (p2 ? hs[15] : hs[11]) : (p2 ? hs[7] : hs[3]));
+    const int d4 = p3 ? d3 + 1 : d3 - 1;
+    if (d4 > kShortLen) {
+        const uint32_t up = p1 ? (p2 ? hs[16] : hs[12]) : (p2 ? hs[8] : hs[4]);
+        const uint32_t dn = p1 ? (p2 ? hs[14] : hs[10]) : hs[6];
+        look(d4, p3 ? up : dn);
+    }
+    SufPay pay{};
+    if (best >= 0) {
+        pay = t.suf_pay[best];
+        if (!suf_equal(pay, best_d, lo, hi)) {
+            best = suf_search_exact(t, Lw, lo, hi);
+            if (best >= 0) pay = t.suf_pay[best];
+        }
+    }
+    if (best >= 0) return SufRef{pay.off, pay.mask, pay.total, 0};
+    return t.suf_short[Lw >= 2 ? short_index(2, window_byte(lo, hi, 0), window_byte(lo, hi, 1))
+                               : short_index(1, window_byte(lo, hi, 0), 0u)];
+}
+
+// Groups a wave's lanes of `in` by the value x: a lane's group's first lane,
+// the group's lanes before it, and its size.
+__device__ __forceinline__ void wave_groups(int32_t x, uint64_t in, int lane, int *lead, int32_t *before,
+                                            int32_t *size) {
+    *lead = lane;
+    *before = 0;
+    *size = 0;
+    while (in) {
+        const int f = __builtin_ctzll(in);
+        const uint64_t same = __ballot(x == __builtin_amdgcn_readlane(x, f)) & in;
+        in &= ~same;
+        if ((same >> lane) & 1u) {
+            *lead = f;
+            *before = __popcll(same & ((1ull << lane) - 1));
+            *size = __popcll(same);
+        }
+    }
+}
+
+// Probe pass: one lane per node m.  A token t of length d that is a suffix of
+// prefix(m) is valid at the ancestor d levels up, node_at[pos - d].  All those of
+// up to kWin bytes come from one search for the longest (suf_search) and are kept
+// as that entry's list and mask (node_suf), 8 bytes per node; the tails of tail
+// compression read their tokens back from there.  Longer tokens are probed where
+// needed (long_hits).
+// Bound by the search's chain of five dependent loads and its VALU work (680
+// instructions per wave); L2 hit rate 0.83.  Probing every length on its own took
+// 14 bucket loads, 4.5 payloads and 64 bytes of hits per node, 101 M L2 requests
+// against 40 M over 5.4 M nodes, and every listed hit an atomic of its own on the few
+// ancestors that neighbouring nodes share: 645 us, now 222 us (370 with the
+// searches alone).
 //   do_mark (a table): every hit whose ancestor has a dense row (row_at of its
 //     blob position; not a tail) is OR-ed into the zeroed table with a 64-bit
 //     atomic, and each block writes the number of valid (node, token) pairs its
@@ -410,126 +559,145 @@ __device__ __forceinline__ int list_span(const DevTables &t, int64_t m) {
 // With tail compression and no table the groups' grid (rg) decides instead:
 // this launch runs its probe blocks blk + blockIdx.x.
 template <bool kCount>
-__global__ void __launch_bounds__(kBlock) k_probe(DevTables t, int64_t m0, int64_t m1, int do_mark,
+__global__ void __launch_bounds__(kBlock, 8) k_probe(DevTables t, int64_t m0, int64_t m1, int do_mark,
                                                   int32_t *__restrict__ pairs, RecGroups rg, int64_t blk) {
-    constexpr int64_t kPer = kBlock / kProbeLanes;  // nodes per block
-    const int64_t gb = blk + blockIdx.x;            // the block in the grid of pairs (and rec_cnt)
+    const int64_t gb = blk + blockIdx.x;  // the block in the grid of pairs (and rec_cnt)
     const int gk = group_of(rg, gb);
-    if (kCount && t.tail_lists) {
-        m0 = pick(rg.n_lo, gk) + (gb - pick(rg.blk0, gk)) * kPer;
+    const bool records = kCount && t.tail_lists;
+    if (records) {
+        m0 = pick(rg.n_lo, gk) + (gb - pick(rg.blk0, gk)) * kBlock;
         m1 = pick(rg.n_hi, gk);
     } else {
-        m0 += (int64_t)blockIdx.x * kPer;
+        m0 += (int64_t)blockIdx.x * kBlock;
     }
-    // lane group g is uniform over a wave (so a wave runs one unrolled path):
-    // wave w of the block takes lengths group w % kProbeLanes of nodes
-    // (w / kProbeLanes) * 64 .. + 63 of the block's kPer
-    const int wv = (int)threadIdx.x / kWave;
-    const int g = wv % kProbeLanes;
-    const int64_t m = m0 + (wv / kProbeLanes) * kWave + (threadIdx.x & (kWave - 1));
+    const int64_t m = m0 + threadIdx.x;
+    // the hits to mark or list, (thread, length - 1) each: the block's threads
+    // share them out, where a loop over a thread's own hits runs as long as the
+    // one with the most, through three dependent trips each
+    __shared__ uint16_t s_item[kBlock * kWin];
+    __shared__ uint32_t s_off[kBlock], s_mask[kBlock];
+    __shared__ int32_t s_pos[kBlock];
+    __shared__ int32_t s_n;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
     int32_t found = 0;
-    // tail_lists: the block's region of its group's records
-    __shared__ int32_t s_rec;  // records the block has written
+    int L = 0;
+    int mspan = INT_MAX, lspan = 0;
+    // what streams through is loaded and stored past the L2's tables
+    const int64_t pos = m < m1 ? __builtin_nontemporal_load(t.node_pos + m) : -1;  // a root ends no token
+    unsigned long long *suf_out = reinterpret_cast<unsigned long long *>(t.node_suf + m);
+    if (m < m1 && pos < 0) __builtin_nontemporal_store(0ull, suf_out);
+    if (pos >= 0) {
+        L = min(__builtin_nontemporal_load(t.depth + m), t.max_len);
+        const int Lw = min(L, kWin);
+        lspan = kCount ? list_span(t, m) : 0;                        // listed up to here
+        const int sspan = t.row_of ? 0 : lspan;                      // short hits listed up to here
+        const int bspan = records ? t.tail_span[m] : INT_MAX;        // (no table) listed beyond
+        if (do_mark) mspan = t.tail_span ? t.tail_span[m] : 0;       // marked beyond
+        SufRef r{0, 0, 0, 0};
+        if (Lw > 0) {
+            uint64_t lo, hi;
+            load_window(t.blob, pos, lo, hi);
+            r = suf_search(t, Lw, lo, hi);
+        }
+        __builtin_nontemporal_store((unsigned long long)r.off | ((unsigned long long)r.mask << 32), suf_out);
+        found = r.total;
+        uint32_t todo = do_mark ? r.mask & ~lengths_to(mspan)
+                                : kCount ? r.mask & (lengths_to(sspan) | ~lengths_to(bspan)) : 0u;
+        if (todo) {
+            s_off[threadIdx.x] = r.off;
+            s_mask[threadIdx.x] = r.mask;
+            s_pos[threadIdx.x] = (int32_t)pos;
+            int32_t at = atomicAdd(&s_n, __popc(todo));
+            for (; todo; todo &= todo - 1) s_item[at++] = (uint16_t)(threadIdx.x << 4 | __builtin_ctz(todo));
+        }
+    }
+    __syncthreads();
+    const int32_t items = s_n;
+    // records: the block's region of its group's records; item i leaves record i
+    __shared__ int32_t s_rec;
     int32_t *rec = nullptr;
     int32_t reg0 = 0, reg1 = 0;
-    if (kCount && t.tail_lists) {
+    if (records) {
         const int64_t o = pick(rg.off0, gk) + (gb - pick(rg.blk0, gk));
         rec = pick(rg.rec, gk);
         reg0 = t.rec_off[o];
         reg1 = t.rec_off[o + 1];
-        if (threadIdx.x == 0) s_rec = 0;
-        __syncthreads();
+        if (threadIdx.x == 0) s_rec = items;
     }
-    const int64_t pos = m < m1 ? t.node_pos[m] : -1;  // a root ends no token
-    if (pos >= 0) {
-        const int L = min(t.depth[m], t.max_len);
-        const int Lw = min(L, kWin);
-        const int lspan = kCount ? list_span(t, m) : 0;              // listed up to here
-        const int sspan = t.row_of ? 0 : lspan;                      // short hits listed up to here
-        const int mspan = do_mark ? (t.tail_span ? t.tail_span[m] : 0) : INT_MAX;  // marked beyond
-        const int bspan = kCount && t.tail_lists ? t.tail_span[m] : INT_MAX;      // (no table) listed beyond
-        unsigned long long *table = reinterpret_cast<unsigned long long *>(t.table);
-        // one hit of length d: the pairs it makes, marked at the table row of
-        // its ancestor (>= 0), counted for its list node (>= 0); without a
-        // table (tail_lists) a listed hit takes its rank in the node's list and
-        // leaves a record in the block's region
-        auto take = [&](int32_t hx, int32_t row, int32_t ln) {
-            if (kCount && t.tail_lists) {
-                const int32_t c = hx >= 0 ? 1 : (int32_t)t.pay[-2 - hx].count;
-                found += c;
-                if (ln < 0) return;
-                const int32_t rank = atomicAdd(&t.count[ln], c);
-                const int32_t at = reg0 + atomicAdd(&s_rec, 1);
-                if (at >= reg1) {  // more records than the host's bound
-                    atomicAdd(t.err, 1);
-                    return;
-                }
-                rec[3 * (int64_t)at] = ln;
-                rec[3 * (int64_t)at + 1] = rank;
-                rec[3 * (int64_t)at + 2] = hx;
-                return;
-            }
-            if (hx >= 0) {
-                if (row >= 0) atomicOr(table + (int64_t)row * t.Wp + (hx >> 6), 1ull << (hx & 63));
-                if (ln >= 0) atomicAdd(&t.count[ln], 1);
-                ++found;
-                return;
-            }
-            const SlotPay mt = t.pay[-2 - hx];  // a string with several token ids (rare)
-            if (ln >= 0) atomicAdd(&t.count[ln], (int32_t)mt.count);
-            found += mt.count;
-            if (row < 0) return;
-            int32_t v = mt.first;
-            for (int k = 0; k < (int)mt.count; ++k) {
-                atomicOr(table + (int64_t)row * t.Wp + (v >> 6), 1ull << (v & 63));
-                v = t.dup_next[v];
-            }
-        };
-        auto list_node = [&](int d) { return kCount && (d <= sspan || d > bspan) ? t.node_at[pos - d] : -1; };
-        auto mark_row = [&](int d) { return d > mspan ? t.row_at[pos - d] : -1; };
-        uint64_t lo, hi;
-        load_window(t.blob, pos, lo, hi);
-        // hit[i]: length d0 + 1 + i; hit[kLaneLens + k]: the short length k + 1 (lane 0)
-        int32_t hit[kLaneLens + kShortLen];
-        const int d0 = g == 0 ? kShortLen : kShortLen + kLaneLens;
-        const uint32_t pending = g == 0 ? probe_lengths<kShortLen>(t, Lw, lo, hi, hit)
-                                        : probe_lengths<kShortLen + kLaneLens>(t, Lw, lo, hi, hit);
-        int32_t n[kLaneLens + kShortLen], r[kLaneLens + kShortLen];
-#pragma unroll
-        for (int k = 0; k < kLaneLens + kShortLen; ++k) {
-            const int d = k < kLaneLens ? d0 + 1 + k : k - kLaneLens + 1;
-            n[k] = hit[k] != -1 ? list_node(d) : -1;
-            r[k] = hit[k] != -1 ? mark_row(d) : -1;
+    unsigned long long *table = reinterpret_cast<unsigned long long *>(t.table);
+    // record i of the block: a hit listed at node ln with its rank in the list
+    auto put = [&](int32_t hx, int32_t ln, int32_t rank, int32_t i) {
+        const int64_t at = (int64_t)reg0 + i;
+        if (at >= reg1) {  // more records than the host's bound
+            atomicAdd(t.err, 1);
+            return;
         }
-        int32_t *hrow = t.hits + m;
-#pragma unroll
-        for (int k = 0; k < kLaneLens + kShortLen; ++k) {
-            const int d = k < kLaneLens ? d0 + 1 + k : k - kLaneLens + 1;
-            if (d <= Lw && (k < kLaneLens || g == 0)) hrow[(int64_t)(d - 1) * t.N] = hit[k];
+        rec[3 * at] = ln;
+        rec[3 * at + 1] = rank;
+        rec[3 * at + 2] = hx;
+    };
+    // one hit: marked at the table row of its ancestor (>= 0), counted for its
+    // list node (>= 0), with records recorded there
+    auto take = [&](int32_t hx, int32_t row, int32_t ln, int32_t i) {
+        if (records) {
+            put(hx, ln, atomicAdd(&t.count[ln], hit_count(t, hx)), i);
+            return;
         }
-#pragma unroll
-        for (int k = 0; k < kLaneLens + kShortLen; ++k)
-            if (hit[k] != -1) take(hit[k], r[k], n[k]);
-        // lengths the home bucket did not settle (rare): the general probe
-        for (uint32_t pm = pending; pm; pm &= pm - 1) {
-            const int d = d0 + 1 + __builtin_ctz(pm);
-            uint32_t hh = kHashSeed;
-            for (int k = 0; k < d; ++k) hh = hash_step(hh, window_byte(lo, hi, k));
-            SlotPay mt;
-            const int32_t sl = probe(t, hash_final(hh), d, lo, hi, pos, &mt);
-            if (sl < 0) continue;
-            const int32_t hx = hit_of_slot(sl, mt.first, mt.count);
-            hrow[(int64_t)(d - 1) * t.N] = hx;
-            take(hx, mark_row(d), list_node(d));
+        if (hx >= 0) {
+            if (row >= 0) atomicOr(table + (int64_t)row * t.Wp + (hx >> 6), 1ull << (hx & 63));
+            if (ln >= 0) atomicAdd(&t.count[ln], 1);
+            return;
         }
-        // tokens longer than the window (rare), by the last lane
-        if (g == kProbeLanes - 1 && L > kWin && (do_mark || lspan > kWin || (kCount && t.tail_lists)))
+        const SlotPay mt = t.pay[-2 - hx];  // a string with several token ids (rare)
+        if (ln >= 0) atomicAdd(&t.count[ln], (int32_t)mt.count);
+        if (row < 0) return;
+        int32_t v = mt.first;
+        for (int k = 0; k < (int)mt.count; ++k) {
+            atomicOr(table + (int64_t)row * t.Wp + (v >> 6), 1ull << (v & 63));
+            v = t.dup_next[v];
+        }
+    };
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t *owner = do_mark ? t.row_at : t.node_at;
+    for (int32_t i0 = 0; i0 < items; i0 += kBlock) {  // uniform over the block
+        const int32_t i = i0 + threadIdx.x;
+        int32_t hx = -1, to = -1, c = 0;
+        if (i < items) {
+            const int l = s_item[i] >> 4, k = s_item[i] & 15;
+            hx = suf_hit(t, s_off[l], s_mask[l], k);
+            to = owner[s_pos[l] - k - 1];
+        }
+        if (!kCount || do_mark) {
+            if (i < items) take(hx, to, -1, i);
+            continue;
+        }
+        // listed: one atomic per list node and wave (neighbouring nodes' hits land on
+        // the same few ancestors, and atomics on one address follow one another)
+        if (i < items) c = hit_count(t, hx);
+        if (__any(c > 1)) {  // a string with several ids among them (rare)
+            if (i < items) take(hx, -1, to, i);
+            continue;
+        }
+        int lead;
+        int32_t before, sum;
+        wave_groups(to, __ballot(i < items), lane, &lead, &before, &sum);
+        int32_t rank = 0;
+        if (i < items && lead == lane) rank = atomicAdd(&t.count[to], sum);
+        rank = __shfl(rank, lead, kWave) + before;
+        if (records && i < items) put(hx, to, rank, i);
+    }
+    // tokens longer than the window (rare), after the items' records
+    if (t.max_len > kWin) {  // uniform over the grid
+        __syncthreads();
+        if (L > kWin && (do_mark || lspan > kWin || records))
             long_hits(t, pos, L, [&](int32_t hx, int d) {
-                take(hx, d > mspan ? t.row_at[pos - d] : -1,
-                     d <= lspan || (kCount && t.tail_lists) ? t.node_at[pos - d] : -1);
+                found += hit_count(t, hx);
+                take(hx, d > mspan ? t.row_at[pos - d] : -1, d <= lspan || records ? t.node_at[pos - d] : -1,
+                     records ? atomicAdd(&s_rec, 1) : 0);
             });
     }
-    if (!do_mark && !(kCount && t.tail_lists)) return;
+    if (!do_mark && !records) return;
     // block sum of the pairs
     __shared__ int32_t wsum[kBlock / kWave];
     for (int o = kWave / 2; o > 0; o >>= 1) found += __shfl_xor(found, o, kWave);
@@ -539,7 +707,7 @@ __global__ void __launch_bounds__(kBlock) k_probe(DevTables t, int64_t m0, int64
         int32_t total = 0;
         for (int w = 0; w < kBlock / kWave; ++w) total += wsum[w];
         pairs[gb] = total;
-        if (kCount && t.tail_lists) t.rec_cnt[gb] = s_rec;
+        if (records) t.rec_cnt[gb] = s_rec;
     }
 }
 
@@ -583,13 +751,11 @@ __global__ void __launch_bounds__(kBlock) k_fill(DevTables t) {
     const int span = list_span(t, m);
     const int Ls = t.row_of ? 0 : min(Lw, span);  // tail compression lists long hits only
     const int bspan = t.tail_lists ? t.tail_span[m] : INT_MAX;  // no table: branching nodes' hits too
-    int32_t s[kWin];
-#pragma unroll
-    for (int d = 1; d <= kWin; ++d)
-        s[d - 1] = d <= Lw && (d <= Ls || d > bspan) ? t.hits[(int64_t)(d - 1) * t.N + m] : -1;
-#pragma unroll
-    for (int d = 1; d <= kWin; ++d)
-        if (s[d - 1] != -1) emit(t, s[d - 1], t.node_at[pos - d]);
+    const NodeSuf r = t.node_suf[m];
+    for (uint32_t todo = r.mask & (lengths_to(Ls) | ~lengths_to(bspan)); todo; todo &= todo - 1) {
+        const int k = __builtin_ctz(todo);
+        emit(t, suf_hit(t, r.off, r.mask, k), t.node_at[pos - k - 1]);
+    }
     if (L > kWin && (span > kWin || t.tail_lists))
         long_hits(t, pos, L, [&](int32_t hx, int d) {
             if (d <= span || t.tail_lists) emit(t, hx, t.node_at[pos - d]);
@@ -723,6 +889,173 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(const int32_t *in, int64_
         for (int k = 0; k < kScanItems; ++k)
             if (base + k < n) out[base + k] = o[k];
     }
+}
+
+// --------------------------------------------------------- suffix table ---
+
+// Built once per vocabulary, after its hash is on the device (see SufPay).
+
+// The scratch set and counts, zero.
+__global__ void __launch_bounds__(kBlock) k_suf_init(SufBuild b) {
+    const int64_t stride = (int64_t)gridDim.x * kBlock, i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    for (int64_t i = i0; i < b.set_slots; i += stride) b.set[i] = 0;
+    for (int64_t i = i0; i < b.buckets; i += stride) {
+        b.cnt[i] = 0;
+        reinterpret_cast<u32x4 *>(b.fps)[i] = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (i0 == 0) *b.counter = 0;
+}
+
+// Every token string's token suffixes of at most kWin bytes (itself included):
+// their lengths, their hits in ascending length, and the ids those stand for.  The
+// strings of one and two bytes also write their places in the short table.
+__global__ void __launch_bounds__(kBlock) k_suf_lists(DevTables t, SufBuild b) {
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    SlotPay p{0, -1, 0, 0};
+    if (q < b.strings) p = t.pay[q];
+    const bool in = p.first >= 0 && (int)p.len <= kWin;
+    const uint64_t lo = p.lo, hi = in ? t.pay_hi[q] : 0ull;
+    int32_t hit[kWin];  // by length - 1
+#pragma unroll
+    for (int k = 0; k < kWin; ++k) hit[k] = -1;
+    uint32_t mask = 0;
+    if (in) {
+        const int L = p.len;
+        int32_t h0[kLaneLens + kShortLen], h1[kLaneLens + kShortLen];
+        const uint32_t p0 = probe_lengths<kShortLen>(t, L, lo, hi, h0);
+        const uint32_t p1 = probe_lengths<kShortLen + kLaneLens>(t, L, lo, hi, h1);
+#pragma unroll
+        for (int k = 0; k < kShortLen; ++k) hit[k] = h0[kLaneLens + k];
+#pragma unroll
+        for (int k = 0; k < kLaneLens; ++k) {
+            hit[kShortLen + k] = h0[k];
+            hit[kShortLen + kLaneLens + k] = h1[k];
+        }
+#pragma unroll
+        for (int k = 0; k < kWin; ++k) {
+            const int j = k - kShortLen;
+            const bool open = j >= 0 && (((j < kLaneLens ? p0 >> j : p1 >> (j - kLaneLens)) & 1u) != 0);
+            if (open) {  // the home bucket did not settle it (rare)
+                uint32_t hh = kHashSeed;
+                for (int i = 0; i <= k; ++i) hh = hash_step(hh, window_byte(lo, hi, i));
+                SlotPay mt;
+                const int32_t sl = probe(t, hash_final(hh), k + 1, lo, hi, 0, &mt);
+                hit[k] = sl >= 0 ? hit_of_slot(sl, mt.first, mt.count) : -1;
+            }
+            if (hit[k] != -1) mask |= 1u << k;
+        }
+    }
+    int32_t total;
+    const int32_t at = block_exclusive_scan(__popc(mask), &total);
+    __shared__ int32_t base;
+    if (threadIdx.x == 0) base = total ? atomicAdd(b.counter, total) : 0;
+    __syncthreads();
+    if (q >= b.strings) return;
+    const uint32_t off = (uint32_t)(base + at);
+    int32_t ids = 0, n = 0;
+#pragma unroll
+    for (int k = 0; k < kWin; ++k)
+        if (hit[k] != -1) {
+            b.id_list[off + n++] = hit[k];
+            ids += hit_count(t, hit[k]);
+        }
+    b.str_off[q] = off;
+    b.str_mask[q] = mask;
+    b.str_total[q] = ids;
+    if (in && (int)p.len <= kShortLen && p.len > 0)
+        b.shrt[short_index(p.len, window_byte(lo, hi, 0), window_byte(lo, hi, 1))] = SufRef{off, mask, ids, 0};
+}
+
+// The rest of the short table: two bytes that are no token have the last byte's
+// suffixes; a byte that is no token has none.
+__global__ void __launch_bounds__(kBlock) k_suf_short(DevTables t, SufBuild b) {
+    const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
+    if (i >= kShortEntries || t.short_hits[i] != -1) return;
+    const int last = i < 256 ? i : (i - 256) & 0xff;
+    b.shrt[i] = i >= 256 && t.short_hits[last] != -1 ? b.shrt[last] : SufRef{0, 0, 0, 0};
+}
+
+// A slot of the scratch set: bits 0..3 the entry's length - 1, bits 4..35 one more
+// than the string it is a suffix of (0: empty slot), then, once it has its place
+// in the table, bits 36..38 its slot and 39..63 how many buckets past its home.
+constexpr int kSetSlotBit = 36, kSetMoveBit = 39;
+
+// The entries: every token string of more than kShortLen bytes and its markers,
+// each distinct one once (the set compares bytes), one thread per string and
+// step of its path.  Bound by its atomics on random lines (83 us for the 1.6 M of
+// 262,144 tokens).  The thread that enters it takes its slot in the table: from its home bucket on, the first bucket that
+// has not been asked for kSufSlots slots before.
+__global__ void __launch_bounds__(kBlock) k_suf_insert(DevTables t, SufBuild b) {
+    const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t q = id >> 2;
+    if (q >= b.strings) return;
+    const SlotPay p = t.pay[q];
+    if (p.first < 0 || (int)p.len <= kShortLen || (int)p.len > kWin) return;
+    int at[4];
+    const int steps = suf_path(p.len, at), j = (int)(id & 3);
+    if (j >= steps) return;
+    const int d = j == 0 ? at[0] : j == 1 ? at[1] : j == 2 ? at[2] : at[3];
+    const uint64_t ml = d >= 8 ? ~0ull : ~0ull >> (64 - 8 * d);
+    const uint64_t mh = d >= 16 ? ~0ull : d <= 8 ? 0ull : ~0ull >> (64 - 8 * (d - 8));
+    const uint64_t lo = p.lo & ml, hi = t.pay_hi[q] & mh;
+    uint32_t h = kHashSeed;
+    for (int k = 0; k < d; ++k) h = hash_step(h, window_byte(lo, hi, k));
+    const uint64_t key = hash_final(h);
+    const unsigned long long code = ((unsigned long long)(q + 1) << 4) | (unsigned)(d - 1);
+    const uint64_t smask = (uint64_t)b.set_slots - 1;
+    // the set is at most half full, so the walk over it ends
+    for (uint64_t i = (key * 0x9e3779b97f4a7c15ull >> 20) & smask;; i = (i + 1) & smask) {
+        unsigned long long *slot = reinterpret_cast<unsigned long long *>(b.set + i);
+        const unsigned long long old = atomicCAS(slot, 0ull, code);
+        if (old == 0) {
+            uint32_t bk = suf_home(key, (uint32_t)b.buckets), moved = 0;
+            int32_t n;
+            // the table has more slots than entries, so a bucket is found
+            while ((n = atomicAdd(&b.cnt[bk], 1)) >= kSufSlots) {
+                bk = bk + 1 == (uint32_t)b.buckets ? 0 : bk + 1;
+                ++moved;
+            }
+            atomicOr(slot, ((unsigned long long)n << kSetSlotBit) | ((unsigned long long)moved << kSetMoveBit));
+            return;
+        }
+        if ((int)(old & 15) == d - 1) {
+            const int64_t o = (int64_t)((old >> 4) & 0xffffffffull) - 1;
+            if (((t.pay[o].lo ^ lo) & ml) == 0 && ((t.pay_hi[o] ^ hi) & mh) == 0) return;
+        }
+    }
+}
+
+// The entries' fingerprints and payloads.
+__global__ void __launch_bounds__(kBlock) k_suf_fill(DevTables t, SufBuild b) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const uint64_t x = i < b.set_slots ? b.set[i] : 0;
+    if (x == 0) return;
+    const int d = (int)(x & 15) + 1;
+    const int64_t q = (int64_t)((x >> 4) & 0xffffffffull) - 1;
+    const uint32_t n = (uint32_t)(x >> kSetSlotBit) & 7u;
+    const uint64_t moved = x >> kSetMoveBit;
+    const uint64_t ml = d >= 8 ? ~0ull : ~0ull >> (64 - 8 * d);
+    const uint64_t mh = d >= 16 ? ~0ull : d <= 8 ? 0ull : ~0ull >> (64 - 8 * (d - 8));
+    SufPay e{};
+    e.lo = t.pay[q].lo & ml;
+    e.hi = t.pay_hi[q] & mh;
+    uint32_t h = kHashSeed;
+    for (int k = 0; k < d; ++k) h = hash_step(h, window_byte(e.lo, e.hi, k));
+    const uint64_t key = hash_final(h);
+    const int64_t bk = (int64_t)((suf_home(key, (uint32_t)b.buckets) + moved) % (uint64_t)b.buckets);
+    const uint32_t all = b.str_mask[q];
+    e.off = b.str_off[q];
+    e.mask = (uint16_t)(all & lengths_to(d));
+    e.len = (uint16_t)d;
+    e.total = __popc((uint32_t)e.mask);
+    if (b.str_total[q] != __popc(all)) {  // strings with several ids among them
+        e.total = 0;
+        for (int k = 0; k < __popc((uint32_t)e.mask); ++k) e.total += hit_count(t, b.id_list[e.off + k]);
+    }
+    b.pay[bk * kSufSlots + n] = e;
+    // slot 7 is taken wherever a key moved on, so its owner says so
+    const uint32_t over = n == kSufSlots - 1 && b.cnt[bk] > kSufSlots ? kSufOver >> 16 : 0u;
+    reinterpret_cast<uint16_t *>(b.fps)[8 * bk + 2 * (n & 3) + (n >> 2)] = (uint16_t)(suf_fingerprint(key) | over);
 }
 
 // ------------------------------------------------------------ row images ---
@@ -949,12 +1282,12 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
     // the row's source (uniform over the block): its dense table row, its list,
     // or (a tail with tail compression) the probe's hits along its path
     const int lane = threadIdx.x & (kWave - 1);
-    // With tail compression most rows are tails: the hits along the path below
-    // n are loaded together with row_of[n] (lane d-1: the hit of node n+d at
-    // distance d), and kept only if n turns out to be a tail.
-    int32_t x_tail = -1;
+    // With tail compression most rows are tails: the suffixes of the nodes on the
+    // path below n are loaded together with row_of[n] (lane d-1: those of node
+    // n+d, one line for all), and kept only if n turns out to be a tail.
+    NodeSuf below{0, 0};
     if (kMode == kApplyTail && live && lane < kWin && lane < t.max_len && (int64_t)n + lane + 1 < t.N)
-        x_tail = t.hits[(int64_t)lane * t.N + n + lane + 1];
+        below = t.node_suf[n + lane + 1];
     int64_t trow = live ? n : -1;
     if (kMode == kApplyTail && live) trow = t.row_of[n];
     const bool tail_row = kMode == kApplyTail && live && trow < 0;
@@ -966,10 +1299,10 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
     for (int u = 0; u < U; ++u) bits[u] = 0;
     const uint32_t lo = (uint32_t)(c0 * E - a);  // first element of the span (wraps below 0 in the first one)
     if (tail_row) {
-        // lane d-1 takes the token of length d starting below the tail (the
-        // path below a tail has consecutive ids, so all of them were loaded)
+        // lane d-1 takes the token of length d that ends at node n+d, if there is
+        // one (the path below a tail has consecutive ids)
         const int Lt = min(min(-1 - (int)trow, kWin), (int)t.max_len);
-        const int32_t x = lane < Lt ? x_tail : -1;
+        const int32_t x = lane < Lt && ((below.mask >> lane) & 1u) ? suf_hit(t, below.off, below.mask, lane) : -1;
         take_ids<E, U>(x >= 0 ? (uint32_t)x - lo : 0xffffffffu, bits);
         // strings with several token ids (rare): walk their id chains
         uint64_t multi = __ballot(x <= -2);
@@ -1419,6 +1752,13 @@ __global__ void __launch_bounds__(kBlock) k_advance(DevTables t, const int32_t *
 
 // ---------------------------------------------------------------- export ---
 
+// Lane d - 1: the hit of length d <= Lt starting below tail n (as in k_apply).
+__device__ __forceinline__ int32_t tail_hit(const DevTables &t, int32_t n, int lane, int Lt) {
+    if (lane >= Lt) return -1;
+    const NodeSuf r = t.node_suf[n + lane + 1];
+    return (r.mask >> lane) & 1u ? suf_hit(t, r.off, r.mask, lane) : -1;
+}
+
 // Rows of the nodes with a dense row; all zero for a dead node and (with tail
 // compression) for a tail, whose bits k_export_tail then sets.
 __global__ void __launch_bounds__(kBlock) k_export_dense(DevTables t, const int32_t *nodes, uint64_t *out) {
@@ -1445,7 +1785,7 @@ __global__ void __launch_bounds__(kBlock) k_export_tail(DevTables t, const int32
     unsigned long long *row = reinterpret_cast<unsigned long long *>(out + r * t.W);
     auto set = [&](int32_t v) { atomicOr(row + (v >> 6), 1ull << (v & 63)); };
     const int Lt = min(min(-1 - trow, kWin), (int)t.max_len);
-    const int32_t x = lane < Lt ? t.hits[(int64_t)lane * t.N + n + lane + 1] : -1;
+    const int32_t x = tail_hit(t, n, lane, Lt);
     if (x >= 0) {
         set(x);
     } else if (x <= -2) {
@@ -1479,7 +1819,7 @@ __global__ void __launch_bounds__(kBlock) k_row_counts(DevTables t, const int32_
         } else {
             if (tail) {  // a tail: the token of length d starting below it is the hit of node n + d
                 const int Lt = min(min(-1 - (int)trow, kWin), (int)t.max_len);
-                const int32_t x = lane < Lt ? t.hits[(int64_t)lane * t.N + n + lane + 1] : -1;
+                const int32_t x = tail_hit(t, n, lane, Lt);
                 c = x >= 0 ? 1 : (x <= -2 ? (int32_t)t.pay[-2 - x].count : 0);
             }
             if ((!t.table || t.tail_long) && lane == 0) c += t.row_ptr[n + 1] - t.row_ptr[n];
@@ -1995,7 +2335,28 @@ hipError_t launch_tok_heads(const uint32_t *tok_off, const uint8_t *tok_blob, in
     return hipGetLastError();
 }
 
-int64_t probe_nodes_per_block() { return kBlock / kProbeLanes; }
+void suf_sizes(SufBuild &b) {
+    // at most 3.2 entries per bucket of eight on average (fewer: equal markers are
+    // one entry), so that one bucket in 200 overflows; the scratch set at most
+    // half full
+    b.buckets = b.entries * 5 / 16 + 64;
+    b.set_slots = 64;
+    while (b.set_slots < 2 * b.entries) b.set_slots <<= 1;
+}
+
+hipError_t launch_suffix_table(const DevTables &t, const SufBuild &b, hipStream_t s) {
+    if (b.strings < 1 || b.buckets < 1 || b.buckets > INT32_MAX / kSufSlots) return hipErrorInvalidValue;
+    const dim3 strings(grid_for(b.strings, kBlock));
+    hipLaunchKernelGGL(k_suf_init, dim3((unsigned)std::min<int64_t>(grid_for(b.set_slots, kBlock), 8192)), dim3(kBlock),
+                       0, s, b);
+    hipLaunchKernelGGL(k_suf_lists, strings, dim3(kBlock), 0, s, t, b);
+    hipLaunchKernelGGL(k_suf_short, dim3(grid_for(kShortEntries, kBlock)), dim3(kBlock), 0, s, t, b);
+    hipLaunchKernelGGL(k_suf_insert, dim3(grid_for(4 * b.strings, kBlock)), dim3(kBlock), 0, s, t, b);
+    hipLaunchKernelGGL(k_suf_fill, dim3(grid_for(b.set_slots, kBlock)), dim3(kBlock), 0, s, t, b);
+    return hipGetLastError();
+}
+
+int64_t probe_nodes_per_block() { return kBlock; }
 
 hipError_t launch_fill_records(const DevTables &t, const RecGroups &rg, hipStream_t s) {
     if (!groups_ok(t, rg)) return hipErrorInvalidValue;
@@ -2017,7 +2378,7 @@ hipError_t launch_zero(uint64_t *p, int64_t words, hipStream_t s) {
     return hipGetLastError();
 }
 
-int64_t mark_blocks(int64_t N) { return (N * kProbeLanes + kBlock - 1) / kBlock; }
+int64_t mark_blocks(int64_t N) { return (N + kBlock - 1) / kBlock; }
 
 int64_t format_blocks(int64_t Wp) { return (Wp * kWave + kBlock - 1) / kBlock; }
 

@@ -191,6 +191,29 @@ struct Arena {
 
 // ------------------------------------------------------------- vocabulary --
 
+// The vocabulary's tables in a DevTables, with the sizes they imply.
+void set_vocab_tables(tam::DevTables &t, const tam_vocab *v) {
+    t.tok_off = v->d_tok_off;
+    t.tok_blob = v->d_tok_blob;
+    t.tok_head = v->d_tok_head;
+    t.fps = v->d_fps;
+    t.pay = v->d_pay;
+    t.pay_hi = v->d_pay_hi;
+    t.short_hits = v->d_short_hits;
+    t.suf_fps = v->suf.fps;
+    t.suf_pay = v->suf.pay;
+    t.suf_short = v->suf.shrt;
+    t.suf_ids = v->suf.id_list;
+    t.dup_next = v->d_dup_next;
+    t.len_present = v->d_len_present;
+    t.slot_mask = (uint64_t)v->fps.size() - 1;
+    t.suf_buckets = (uint32_t)v->suf.buckets;
+    t.len_mask = v->len_mask;
+    t.max_len = (int32_t)v->max_tok_len;
+    t.V = v->V;
+    t.W = v->W;
+}
+
 void vocab_release(tam_vocab *v) {
     if (!v) return;
     if (v->refs.fetch_sub(1) != 1) return;
@@ -253,6 +276,17 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     const size_t o_short = a.take<int32_t>((int64_t)v->short_hits.size());
     const size_t o_dup = a.take<int32_t>(V);
     const size_t o_len = a.take<uint8_t>((int64_t)v->len_present.size());
+    tam::SufBuild &sb = v->suf;
+    sb.strings = (int64_t)v->pay.size();
+    tam::suf_sizes(sb);
+    const size_t o_str_off = a.take<uint32_t>(sb.strings), o_str_mask = a.take<uint32_t>(sb.strings);
+    const size_t o_str_total = a.take<int32_t>(sb.strings);
+    const size_t o_set = a.take<uint64_t>(sb.set_slots), o_cnt = a.take<int32_t>(sb.buckets);
+    const size_t o_counter = a.take<int32_t>(1);
+    const size_t o_suf_fps = a.take<uint32_t>(4 * sb.buckets);
+    const size_t o_suf_pay = a.take<tam::SufPay>(tam::kSufSlots * sb.buckets);
+    const size_t o_suf_short = a.take<tam::SufRef>(tam::kShortEntries);
+    const size_t o_suf_ids = a.take<int32_t>(sb.ids);
     uint8_t *base = static_cast<uint8_t *>(alloc_with(v->own_alloc, v->alloc, a.used));
     if (!base) {
         delete v;
@@ -269,6 +303,16 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     v->d_short_hits = reinterpret_cast<const int32_t *>(base + o_short);
     v->d_dup_next = reinterpret_cast<const int32_t *>(base + o_dup);
     v->d_len_present = base + o_len;
+    sb.str_off = reinterpret_cast<uint32_t *>(base + o_str_off);
+    sb.str_mask = reinterpret_cast<uint32_t *>(base + o_str_mask);
+    sb.str_total = reinterpret_cast<int32_t *>(base + o_str_total);
+    sb.set = reinterpret_cast<uint64_t *>(base + o_set);
+    sb.cnt = reinterpret_cast<int32_t *>(base + o_cnt);
+    sb.counter = reinterpret_cast<int32_t *>(base + o_counter);
+    sb.fps = reinterpret_cast<uint32_t *>(base + o_suf_fps);
+    sb.pay = reinterpret_cast<tam::SufPay *>(base + o_suf_pay);
+    sb.shrt = reinterpret_cast<tam::SufRef *>(base + o_suf_short);
+    sb.id_list = reinterpret_cast<int32_t *>(base + o_suf_ids);
     auto up = [&](size_t off, const void *src, size_t bytes) -> hipError_t {
         if (bytes == 0) return hipSuccess;
         return hipMemcpyAsync(base + off, src, bytes, hipMemcpyHostToDevice, s);
@@ -283,6 +327,11 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     if (e == hipSuccess) e = up(o_len, v->len_present.data(), v->len_present.size());
     if (e == hipSuccess)
         e = tam::launch_tok_heads(v->d_tok_off, v->d_tok_blob, V, reinterpret_cast<tam::TokHead *>(base + o_head), s);
+    if (e == hipSuccess) {
+        tam::DevTables t{};
+        set_vocab_tables(t, v);
+        e = tam::launch_suffix_table(t, sb, s);
+    }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ready, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(v->ready, s);
     v->upload_ms = ms_since(t1);
@@ -457,15 +506,7 @@ void set_trie_tables(tam::DevTables &t, const tam_handle *h, const tam_vocab *v,
     t.depth = reinterpret_cast<const int32_t *>(tb + o_depth);
     t.walk = reinterpret_cast<const tam::Walk *>(tb + o_walk);
     t.kid = reinterpret_cast<const tam::Kid *>(tb + o_kid);
-    t.tok_off = v->d_tok_off;
-    t.tok_blob = v->d_tok_blob;
-    t.tok_head = v->d_tok_head;
-    t.fps = v->d_fps;
-    t.pay = v->d_pay;
-    t.pay_hi = v->d_pay_hi;
-    t.short_hits = v->d_short_hits;
-    t.dup_next = v->d_dup_next;
-    t.len_present = v->d_len_present;
+    set_vocab_tables(t, v);
     t.table = nullptr;
     t.sub_end = nullptr;
     t.tail_span = nullptr;
@@ -477,13 +518,8 @@ void set_trie_tables(tam::DevTables &t, const tam_handle *h, const tam_vocab *v,
     t.rec_off = nullptr;
     t.rec_cnt = nullptr;
     t.N = h->N;
-    t.V = v->V;
-    t.W = v->W;
     t.Wp = (v->W + 7) & ~int64_t(7);
     t.blob_bytes = h->blob_bytes;
-    t.slot_mask = (uint64_t)v->fps.size() - 1;
-    t.len_mask = v->len_mask;
-    t.max_len = (int32_t)v->max_tok_len;
     t.terminator = h->terminator;
     t.classes = nullptr;
     t.fmt_L = -1;
@@ -549,7 +585,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
                             !(o.flags & TAM_FLAG_LAZY_ROWS);
     size_t o_pairs_t = 0, o_rec_off_t = 0, o_rec_cnt_t = 0;
     int64_t next_blk = 0, next_off = 0, listed_total = 0;  // early_tail: the groups' blocks, offsets, records
-    size_t o_hits = 0, o_count = 0, o_kid_cnt = 0, o_kid_parent = 0, o_kid_rank = 0, o_kid_total = 0, o_strs = 0, o_err = 0;
+    size_t o_suf = 0, o_count = 0, o_kid_cnt = 0, o_kid_parent = 0, o_kid_rank = 0, o_kid_total = 0, o_strs = 0, o_err = 0;
     tam::DevTables te{};  // the trie and vocabulary tables the early counts read
     bool enqueued = false;  // device work that reads host tables or writes device memory
     double hook_ms = 0;     // time spent in the two hooks (allocation and enqueue)
@@ -578,7 +614,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         o_row_of = ta.take<int32_t>(split ? hh->N : 0);
         o_row_at = ta.take<int32_t>(split ? hh->blob_bytes : 0);
         o_tail_rec = ta.take<tam::TailRec>(split ? hh->K_unique : 0);
-        o_hits = ta.take<int32_t>(early_count || early_tail ? tam::kWin * hh->N : 0);
+        o_suf = ta.take<tam::NodeSuf>(early_count || early_tail ? hh->N : 0);
         o_count = ta.take<int32_t>(early_count || early_tail ? hh->N : 0);
         // a group's blocks start a new block of nodes: at most one more block
         // than the whole range per group
@@ -624,7 +660,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
             te.rec_cnt = reinterpret_cast<int32_t *>(trie_base + o_rec_cnt_t);
         }
         if (early_count || early_tail) {
-            te.hits = reinterpret_cast<int32_t *>(trie_base + o_hits);
+            te.node_suf = reinterpret_cast<tam::NodeSuf *>(trie_base + o_suf);
             te.count = reinterpret_cast<int32_t *>(trie_base + o_count);
             hipError_t e = hipStreamWaitEvent(s, vocab->ready, 0);
             const bool timing = (hh->flags & TAM_FLAG_TIMING) != 0;
@@ -817,7 +853,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
     // counts of early list counts are in the trie's allocation)
     const int64_t NP = lazy ? 0 : h->N;
     const bool early = early_count || early_tail;  // hits and counts are in the trie's allocation
-    const size_t o_hits_b = a.take<int32_t>(early ? 0 : tam::kWin * NP);
+    const size_t o_suf_b = a.take<tam::NodeSuf>(early ? 0 : NP);
     const size_t o_count_b = a.take<int32_t>(early ? 0 : NP);
     const size_t o_row_ptr = a.take<int32_t>(NP + 1);
     const size_t o_cursor = a.take<int32_t>(NP);
@@ -861,7 +897,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
     tam::DevTables &t = h->dt;
     set_trie_tables(t, h, vocab, trie_base, o_blob, o_node_at, o_node_pos, o_depth, o_walk, o_kid);
     t.err = h->d_err;
-    t.hits = early ? te.hits : reinterpret_cast<int32_t *>(base + o_hits_b);
+    t.node_suf = early ? te.node_suf : reinterpret_cast<tam::NodeSuf *>(base + o_suf_b);
     t.count = early ? te.count : reinterpret_cast<int32_t *>(base + o_count_b);
     t.row_ptr = reinterpret_cast<int32_t *>(base + o_row_ptr);
     t.cursor = reinterpret_cast<int32_t *>(base + o_cursor);
@@ -1015,24 +1051,12 @@ tam_status compile_format(const uint8_t *classes, int64_t L, tam_vocab *vocab, c
     h->pairs = reinterpret_cast<int32_t *>(base + o_pairs);
     tam::DevTables &t = h->dt;
     t = tam::DevTables{};
-    t.tok_off = vocab->d_tok_off;
-    t.tok_blob = vocab->d_tok_blob;
-    t.fps = vocab->d_fps;
-    t.pay = vocab->d_pay;
-    t.pay_hi = vocab->d_pay_hi;
-    t.short_hits = vocab->d_short_hits;
-    t.dup_next = vocab->d_dup_next;
-    t.len_present = vocab->d_len_present;
+    set_vocab_tables(t, vocab);
     t.table = table;
     t.row_at = nullptr;
     t.N = N;
-    t.V = h->V;
-    t.W = h->W;
     t.Wp = h->Wp;
     t.R = N;
-    t.slot_mask = (uint64_t)vocab->fps.size() - 1;
-    t.len_mask = vocab->len_mask;
-    t.max_len = (int32_t)vocab->max_tok_len;
     t.terminator = T;
     t.classes = base + o_cls;
     t.fmt_L = (int32_t)L;

@@ -95,6 +95,26 @@ hipError_t launch_lay(const StrRec *strs, const TailRec *trec, int64_t s0, int64
 hipError_t launch_kids(const StrRec *strs, int64_t K, int64_t N, Walk *walk, Kid *kid, const int32_t *kid_cnt,
                        const int32_t *kid_parent, const int32_t *kid_rank, int32_t *kid_total, int32_t *err,
                        hipStream_t s);
+// The suffix table of a vocabulary whose hash (t: fps, pay, pay_hi, short_hits)
+// is on the device: scratch and outputs as sized by suf_sizes.
+struct SufBuild {
+    int64_t strings = 0;   // distinct token strings (at least 1)
+    int64_t entries = 0;   // upper bound on tokens and markers
+    int64_t ids = 0;       // upper bound on the lists' lengths together
+    int64_t buckets = 0;   // of the table
+    int64_t set_slots = 0; // of the scratch set that finds equal markers, a power of two
+    uint32_t *str_off, *str_mask;  // [strings] scratch
+    int32_t *str_total;            // [strings] scratch
+    uint64_t *set;                 // [set_slots] scratch
+    int32_t *cnt;                  // [buckets] scratch
+    int32_t *counter;              // [1] scratch
+    uint32_t *fps;                 // [4 * buckets]
+    SufPay *pay;                   // [8 * buckets]
+    SufRef *shrt;                  // [kShortEntries]
+    int32_t *id_list;              // [ids]
+};
+void suf_sizes(SufBuild &b);  // buckets and set_slots from entries
+hipError_t launch_suffix_table(const DevTables &t, const SufBuild &b, hipStream_t s);
 // the heads of V tokens
 hipError_t launch_tok_heads(const uint32_t *tok_off, const uint8_t *tok_blob, int64_t V, TokHead *head, hipStream_t s);
 hipError_t launch_scan(const DevTables &t, hipStream_t s);
@@ -181,6 +201,7 @@ struct tam_vocab {
     const tam::SlotPay *d_pay = nullptr;
     const uint64_t *d_pay_hi = nullptr;
     const int32_t *d_short_hits = nullptr;
+    tam::SufBuild suf{};  // the suffix table, built on the device
     const int32_t *d_dup_next = nullptr;
     const uint8_t *d_len_present = nullptr;
     hipEvent_t ready = nullptr;  // recorded after the uploads

@@ -1100,6 +1100,29 @@ def test_apply_two_chunks_per_thread(P, flags, V):
         assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, off)
 
 
+@pytest.mark.parametrize("lengths", [[d] for d in range(1, 18)] + [[1, 16], [2, 9], [3, 13, 16], [8, 10, 12], [4, 5, 17, 30],
+                                                                    list(range(1, 17)), list(range(1, 20))],
+                         ids=lambda x: "-".join(map(str, x)) if len(x) < 6 else "1..%d" % x[-1])
+def test_suffix_search_lengths(P, lengths):
+    """Vocabularies whose tokens have only the given lengths (every path of the
+    search over lengths, markers without tokens and tokens that are markers
+    too), some with several ids, over sets that share long suffixes."""
+    rng = np.random.default_rng(sum(lengths) + 100 * len(lengths))
+    words = [b"".join(rng.choice([b"a", b"b"], size=int(n))) for n in rng.integers(1, 9, size=12)]
+    strings = list(dict.fromkeys(b"".join(words[int(i)] for i in rng.integers(0, 12, size=int(k)))
+                                 for k in rng.integers(1, 9, size=60)))
+    vocab = [b"", b"zz"]
+    for d in lengths:
+        for _ in range(40):
+            s = strings[int(rng.integers(0, len(strings)))] + b'"'
+            if len(s) >= d:
+                at = int(rng.integers(0, len(s) - d + 1))
+                vocab.append(s[at:at + d])
+            vocab.append(b"".join(rng.choice([b"a", b"b"], size=d)))
+    for flags in FLAGS:
+        full_check(P, strings, vocab, flags=flags)[0].close()
+
+
 def test_many_rows_grid_split(P):
     """More than 65,535 batch rows in one call (the launcher splits the grid)."""
     strings = [b"ab", b"b"]
