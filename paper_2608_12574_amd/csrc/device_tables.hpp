@@ -254,6 +254,7 @@ struct DevTables {
     int64_t blob_bytes;
     uint64_t slot_mask;         // slots - 1 (slots = a power of two, >= kBucket)
     uint32_t suf_buckets;
+    int32_t suf_dups;           // some token string has several ids
     uint64_t len_mask;          // bit d (d < 64): some token has length d
     int32_t max_len;
     int32_t terminator;

@@ -692,6 +692,7 @@ tam_status build_vocab(const uint8_t *tb, const int64_t *to, int64_t V, tam_voca
         for (const auto &d : part)
             for (int64_t l = 0; l <= max_len; ++l) dup[(size_t)l] = std::max(dup[(size_t)l], d[(size_t)l]);
     }
+    for (int64_t l = 0; l <= max_len; ++l) h->dups |= dup[(size_t)l] > 1;
     h->dup_cum.assign((size_t)max_len + 1, 0);
     for (int64_t d = 1; d <= max_len; ++d) h->dup_cum[(size_t)d] = h->dup_cum[(size_t)d - 1] + dup[(size_t)d];
     return TAM_OK;

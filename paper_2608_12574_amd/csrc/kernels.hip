@@ -558,42 +558,56 @@ __device__ __forceinline__ void wave_groups(int32_t x, uint64_t in, int lane, in
 // forest) one group of whole sets, whose nodes' ancestors are in the group too.
 // With tail compression and no table the groups' grid (rg) decides instead:
 // this launch runs its probe blocks blk + blockIdx.x.
-template <bool kCount>
+// kRecords (tail lists) shares the hits out over the block; the others take them
+// length by length, unrolled.
+template <bool kCount, bool kRecords>
 __global__ void __launch_bounds__(kBlock, 8) k_probe(DevTables t, int64_t m0, int64_t m1, int do_mark,
-                                                  int32_t *__restrict__ pairs, RecGroups rg, int64_t blk) {
+                                                     int32_t *__restrict__ pairs, RecGroups rg, int64_t blk) {
     const int64_t gb = blk + blockIdx.x;  // the block in the grid of pairs (and rec_cnt)
-    const int gk = group_of(rg, gb);
-    const bool records = kCount && t.tail_lists;
-    if (records) {
+    const int gk = kRecords ? group_of(rg, gb) : 0;
+    if (kRecords) {
         m0 = pick(rg.n_lo, gk) + (gb - pick(rg.blk0, gk)) * kBlock;
         m1 = pick(rg.n_hi, gk);
     } else {
         m0 += (int64_t)blockIdx.x * kBlock;
     }
     const int64_t m = m0 + threadIdx.x;
-    // the hits to mark or list, (thread, length - 1) each: the block's threads
-    // share them out, where a loop over a thread's own hits runs as long as the
-    // one with the most, through three dependent trips each
-    __shared__ uint16_t s_item[kBlock * kWin];
-    __shared__ uint32_t s_off[kBlock], s_mask[kBlock];
-    __shared__ int32_t s_pos[kBlock];
-    __shared__ int32_t s_n;
-    if (threadIdx.x == 0) s_n = 0;
-    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    // records: the listed hits of the block, (thread, length - 1) each, and what
+    // their threads found
+    __shared__ uint16_t s_item[kRecords ? kBlock * kWin : 1];
+    __shared__ uint32_t s_off[kRecords ? kBlock : 1], s_mask[kRecords ? kBlock : 1];
+    __shared__ int32_t s_pos[kRecords ? kBlock : 1];
+    __shared__ int32_t s_n;  // hits, then records left
+    if (kRecords) {
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+    }
     int32_t found = 0;
-    int L = 0;
-    int mspan = INT_MAX, lspan = 0;
+    int L = 0, lspan = 0, mspan = INT_MAX;
     // what streams through is loaded and stored past the L2's tables
     const int64_t pos = m < m1 ? __builtin_nontemporal_load(t.node_pos + m) : -1;  // a root ends no token
     unsigned long long *suf_out = reinterpret_cast<unsigned long long *>(t.node_suf + m);
     if (m < m1 && pos < 0) __builtin_nontemporal_store(0ull, suf_out);
+    unsigned long long *table = reinterpret_cast<unsigned long long *>(t.table);
+    auto mark = [&](int32_t hx, int32_t row) {
+        if (row < 0) return;
+        if (hx >= 0) {
+            atomicOr(table + (int64_t)row * t.Wp + (hx >> 6), 1ull << (hx & 63));
+            return;
+        }
+        const SlotPay mt = t.pay[-2 - hx];  // a string with several token ids (rare)
+        int32_t v = mt.first;
+        for (int k = 0; k < (int)mt.count; ++k) {
+            atomicOr(table + (int64_t)row * t.Wp + (v >> 6), 1ull << (v & 63));
+            v = t.dup_next[v];
+        }
+    };
     if (pos >= 0) {
         L = min(__builtin_nontemporal_load(t.depth + m), t.max_len);
         const int Lw = min(L, kWin);
-        lspan = kCount ? list_span(t, m) : 0;                        // listed up to here
-        const int sspan = t.row_of ? 0 : lspan;                      // short hits listed up to here
-        const int bspan = records ? t.tail_span[m] : INT_MAX;        // (no table) listed beyond
-        if (do_mark) mspan = t.tail_span ? t.tail_span[m] : 0;       // marked beyond
+        lspan = kCount ? list_span(t, m) : 0;  // listed up to here
+        if (do_mark) mspan = t.tail_span ? t.tail_span[m] : 0;  // marked beyond
         SufRef r{0, 0, 0, 0};
         if (Lw > 0) {
             uint64_t lo, hi;
@@ -602,30 +616,47 @@ __global__ void __launch_bounds__(kBlock, 8) k_probe(DevTables t, int64_t m0, in
         }
         __builtin_nontemporal_store((unsigned long long)r.off | ((unsigned long long)r.mask << 32), suf_out);
         found = r.total;
-        uint32_t todo = do_mark ? r.mask & ~lengths_to(mspan)
-                                : kCount ? r.mask & (lengths_to(sspan) | ~lengths_to(bspan)) : 0u;
-        if (todo) {
-            s_off[threadIdx.x] = r.off;
-            s_mask[threadIdx.x] = r.mask;
-            s_pos[threadIdx.x] = (int32_t)pos;
-            int32_t at = atomicAdd(&s_n, __popc(todo));
-            for (; todo; todo &= todo - 1) s_item[at++] = (uint16_t)(threadIdx.x << 4 | __builtin_ctz(todo));
+        if (kRecords) {  // on the branching ancestors, beyond the tails
+            uint32_t todo = r.mask & ~lengths_to(lspan);
+            if (todo) {
+                s_off[threadIdx.x] = r.off;
+                s_mask[threadIdx.x] = r.mask;
+                s_pos[threadIdx.x] = (int32_t)pos;
+                int32_t at = atomicAdd(&s_n, __popc(todo));
+                for (; todo; todo &= todo - 1) s_item[at++] = (uint16_t)(threadIdx.x << 4 | __builtin_ctz(todo));
+            }
+        } else {
+            // One length after another and unrolled, so that the loads of all come
+            // before the first atomic, and the lanes of an atomic have different
+            // ancestors (those of consecutive nodes are consecutive).
+            const uint32_t todo = do_mark ? r.mask & ~lengths_to(mspan)
+                                          : kCount && !t.row_of ? r.mask & lengths_to(lspan) : 0u;
+            const int32_t *owner = do_mark ? t.row_at : t.node_at;
+            const bool one_each = r.total == __popc(r.mask);  // no string with several ids
+            constexpr int H = kWin / 2;
+#pragma unroll
+            for (int h = 0; h < kWin; h += H) {
+                if (!__any((todo >> h) & ((1u << H) - 1u))) continue;
+                int32_t hx[H], to[H];
+#pragma unroll
+                for (int j = 0; j < H; ++j) {
+                    const bool on = (todo >> (h + j)) & 1u;
+                    hx[j] = on && (do_mark || !one_each) ? suf_hit(t, r.off, r.mask, h + j) : 0;
+                    to[j] = on ? owner[pos - h - j - 1] : -1;
+                }
+#pragma unroll
+                for (int j = 0; j < H; ++j) {
+                    if (!((todo >> (h + j)) & 1u)) continue;
+                    if (!kCount || do_mark)
+                        mark(hx[j], to[j]);
+                    else
+                        atomicAdd(&t.count[to[j]], hit_count(t, hx[j]));
+                }
+            }
         }
     }
-    __syncthreads();
-    const int32_t items = s_n;
-    // records: the block's region of its group's records; item i leaves record i
-    __shared__ int32_t s_rec;
     int32_t *rec = nullptr;
     int32_t reg0 = 0, reg1 = 0;
-    if (records) {
-        const int64_t o = pick(rg.off0, gk) + (gb - pick(rg.blk0, gk));
-        rec = pick(rg.rec, gk);
-        reg0 = t.rec_off[o];
-        reg1 = t.rec_off[o + 1];
-        if (threadIdx.x == 0) s_rec = items;
-    }
-    unsigned long long *table = reinterpret_cast<unsigned long long *>(t.table);
     // record i of the block: a hit listed at node ln with its rank in the list
     auto put = [&](int32_t hx, int32_t ln, int32_t rank, int32_t i) {
         const int64_t at = (int64_t)reg0 + i;
@@ -637,91 +668,89 @@ __global__ void __launch_bounds__(kBlock, 8) k_probe(DevTables t, int64_t m0, in
         rec[3 * at + 1] = rank;
         rec[3 * at + 2] = hx;
     };
-    // one hit: marked at the table row of its ancestor (>= 0), counted for its
-    // list node (>= 0), with records recorded there
-    auto take = [&](int32_t hx, int32_t row, int32_t ln, int32_t i) {
-        if (records) {
-            put(hx, ln, atomicAdd(&t.count[ln], hit_count(t, hx)), i);
-            return;
-        }
-        if (hx >= 0) {
-            if (row >= 0) atomicOr(table + (int64_t)row * t.Wp + (hx >> 6), 1ull << (hx & 63));
-            if (ln >= 0) atomicAdd(&t.count[ln], 1);
-            return;
-        }
-        const SlotPay mt = t.pay[-2 - hx];  // a string with several token ids (rare)
-        if (ln >= 0) atomicAdd(&t.count[ln], (int32_t)mt.count);
-        if (row < 0) return;
-        int32_t v = mt.first;
-        for (int k = 0; k < (int)mt.count; ++k) {
-            atomicOr(table + (int64_t)row * t.Wp + (v >> 6), 1ull << (v & 63));
-            v = t.dup_next[v];
-        }
-    };
-    const int lane = threadIdx.x & (kWave - 1);
-    const int32_t *owner = do_mark ? t.row_at : t.node_at;
-    for (int32_t i0 = 0; i0 < items; i0 += kBlock) {  // uniform over the block
-        const int32_t i = i0 + threadIdx.x;
-        int32_t hx = -1, to = -1, c = 0;
-        if (i < items) {
-            const int l = s_item[i] >> 4, k = s_item[i] & 15;
-            hx = suf_hit(t, s_off[l], s_mask[l], k);
-            to = owner[s_pos[l] - k - 1];
-        }
-        if (!kCount || do_mark) {
-            if (i < items) take(hx, to, -1, i);
-            continue;
-        }
-        // listed: one atomic per list node and wave (neighbouring nodes' hits land on
-        // the same few ancestors, and atomics on one address follow one another)
-        if (i < items) c = hit_count(t, hx);
-        if (__any(c > 1)) {  // a string with several ids among them (rare)
-            if (i < items) take(hx, -1, to, i);
-            continue;
-        }
-        int lead;
-        int32_t before, sum;
-        wave_groups(to, __ballot(i < items), lane, &lead, &before, &sum);
-        int32_t rank = 0;
-        if (i < items && lead == lane) rank = atomicAdd(&t.count[to], sum);
-        rank = __shfl(rank, lead, kWave) + before;
-        if (records && i < items) put(hx, to, rank, i);
-    }
-    // tokens longer than the window (rare), after the items' records
-    if (t.max_len > kWin) {  // uniform over the grid
+    if (kRecords) {
+        // Only nodes near a branch have listed hits, a few lanes of a wave, and
+        // neighbouring nodes' hits land on the same few ancestors.  So the block's
+        // threads share the hits out, and a wave counts those of one list node with
+        // one atomic (atomics on one address follow one another): over a forest of
+        // 5.4 M nodes 222 us for the pass, 370 with an atomic each, 382 with a
+        // loop over each lane's own hits; over 1,000 word strings 49.6 against 59.1 us
+        // per step with an atomic each.
         __syncthreads();
-        if (L > kWin && (do_mark || lspan > kWin || records))
+        const int32_t items = s_n;
+        const int64_t o = pick(rg.off0, gk) + (gb - pick(rg.blk0, gk));
+        rec = pick(rg.rec, gk);
+        reg0 = t.rec_off[o];
+        reg1 = t.rec_off[o + 1];
+        for (int32_t i0 = 0; i0 < items; i0 += kBlock) {  // uniform over the block
+            const int32_t i = i0 + threadIdx.x;
+            const bool in = i < items;
+            int32_t hx = -1, ln = -1, c = 0;
+            if (in) {
+                const int l = s_item[i] >> 4, k = s_item[i] & 15;
+                hx = suf_hit(t, s_off[l], s_mask[l], k);
+                ln = t.node_at[s_pos[l] - k - 1];
+                c = hit_count(t, hx);
+            }
+            int32_t rank = 0;
+            if (__any(c > 1)) {  // a string with several ids among them (rare)
+                if (in) rank = atomicAdd(&t.count[ln], c);
+            } else {
+                int lead;
+                int32_t before, sum;
+                wave_groups(ln, __ballot(in), lane, &lead, &before, &sum);
+                if (in && lead == lane) rank = atomicAdd(&t.count[ln], sum);
+                rank = __shfl(rank, lead, kWave) + before;
+            }
+            if (in) put(hx, ln, rank, i);
+        }
+    }
+    // tokens longer than the window (rare), after the shared hits' records
+    if (t.max_len > kWin) {  // uniform over the grid
+        if (kRecords) __syncthreads();
+        if (L > kWin && (do_mark || lspan > kWin || kRecords))
             long_hits(t, pos, L, [&](int32_t hx, int d) {
-                found += hit_count(t, hx);
-                take(hx, d > mspan ? t.row_at[pos - d] : -1, d <= lspan || records ? t.node_at[pos - d] : -1,
-                     records ? atomicAdd(&s_rec, 1) : 0);
+                const int32_t c = hit_count(t, hx);
+                found += c;
+                if (d > mspan) mark(hx, t.row_at[pos - d]);
+                if (kRecords) {
+                    const int32_t ln = t.node_at[pos - d], rank = atomicAdd(&t.count[ln], c);
+                    put(hx, ln, rank, atomicAdd(&s_n, 1));
+                } else if (d <= lspan) {
+                    atomicAdd(&t.count[t.node_at[pos - d]], c);
+                }
             });
     }
-    if (!do_mark && !records) return;
+    if (!do_mark && !kRecords) return;
     // block sum of the pairs
     __shared__ int32_t wsum[kBlock / kWave];
     for (int o = kWave / 2; o > 0; o >>= 1) found += __shfl_xor(found, o, kWave);
-    if ((threadIdx.x & (kWave - 1)) == 0) wsum[threadIdx.x / kWave] = found;
+    if (lane == 0) wsum[threadIdx.x / kWave] = found;
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t total = 0;
         for (int w = 0; w < kBlock / kWave; ++w) total += wsum[w];
         pairs[gb] = total;
-        if (records) t.rec_cnt[gb] = s_rec;
+        if (kRecords) t.rec_cnt[gb] = s_n;
     }
 }
+
+// Threads per probe block's records: one record per thread in a few rounds also
+// where most hits are listed (a forest of small word sets, about 1,000 per block: with
+// one wave 6 us more per rebuild).
+constexpr int kFillThreads = 256;
 
 // The records of probe block blockIdx.x of the groups' grid (tail compression
 // without a table): each listed hit's ids go to its node's list at
 // row_ptr[node] + rank.
-__global__ void __launch_bounds__(kWave) k_fill_records(DevTables t, RecGroups rg) {
+__global__ void __launch_bounds__(kFillThreads) k_fill_records(DevTables t, RecGroups rg) {
     const int64_t b = blockIdx.x;
     const int gk = group_of(rg, b);
     const int64_t o = pick(rg.off0, gk) + (b - pick(rg.blk0, gk));
     const int64_t r0 = t.rec_off[o];
     const int32_t n = min(t.rec_cnt[b], t.rec_off[o + 1] - t.rec_off[o]);
     const int32_t *rec = pick(rg.rec, gk);
-    for (int32_t i = threadIdx.x; i < n; i += kWave) {
+    for (int32_t i = threadIdx.x; i < n; i += kFillThreads) {
         const int32_t *r = rec + 3 * (r0 + i);
         const int32_t ln = r[0], rank = r[1], hx = r[2];
         const int64_t at = (int64_t)t.row_ptr[ln] + rank;
@@ -752,10 +781,28 @@ __global__ void __launch_bounds__(kBlock) k_fill(DevTables t) {
     const int Ls = t.row_of ? 0 : min(Lw, span);  // tail compression lists long hits only
     const int bspan = t.tail_lists ? t.tail_span[m] : INT_MAX;  // no table: branching nodes' hits too
     const NodeSuf r = t.node_suf[m];
-    for (uint32_t todo = r.mask & (lengths_to(Ls) | ~lengths_to(bspan)); todo; todo &= todo - 1) {
-        const int k = __builtin_ctz(todo);
-        emit(t, suf_hit(t, r.off, r.mask, k), t.node_at[pos - k - 1]);
+    const uint32_t todo = r.mask & (lengths_to(Ls) | ~lengths_to(bspan));
+    int32_t s[kWin], to[kWin];
+#pragma unroll
+    for (int k = 0; k < kWin; ++k) {
+        const bool on = (todo >> k) & 1u;
+        s[k] = on ? suf_hit(t, r.off, r.mask, k) : -1;
+        to[k] = on ? t.node_at[pos - k - 1] : -1;
     }
+    // the places of all (one returning atomic each) before the first store
+    int32_t at[kWin];
+#pragma unroll
+    for (int k = 0; k < kWin; ++k)
+        if (s[k] >= 0) at[k] = t.row_ptr[to[k]] + atomicAdd(&t.cursor[to[k]], 1);
+#pragma unroll
+    for (int k = 0; k < kWin; ++k)
+        if (s[k] >= 0) t.entries[at[k]] = s[k];
+    if (t.suf_dups)  // strings with several ids
+        for (uint32_t left = todo; left; left &= left - 1) {
+            const int k = __builtin_ctz(left);
+            const int32_t x = suf_hit(t, r.off, r.mask, k);
+            if (x < -1) emit(t, x, t.node_at[pos - k - 1]);
+        }
     if (L > kWin && (span > kWin || t.tail_lists))
         long_hits(t, pos, L, [&](int32_t hx, int d) {
             if (d <= span || t.tail_lists) emit(t, hx, t.node_at[pos - d]);
@@ -852,11 +899,19 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(int32_t *sums, int64_t nb, 
     if (threadIdx.x == 0) *total_out = carry;
 }
 
-// The scan's second pass.  own_prefix (nb <= kScanTile): each block adds up the
-// block sums before its own (at most kScanTile of them, from L2) and the last
-// block writes the grand total; otherwise sums holds k_scan_top's prefixes.
+// The scan's second pass, by how a block learns the sum before its own:
+// kScanSelf (few blocks: the only pass) reads the counts themselves; kScanOwn (nb
+// <= kScanTile) adds up the block sums before its own (at most kScanTile of them,
+// from L2); kScanTop takes it from k_scan_top's prefixes.  Without k_scan_top the
+// last block writes the grand total.  zero (or null): n values set to 0.
+constexpr int kScanTop = 0, kScanOwn = 1, kScanSelf = 2;
+// Counting again costs a block 16 KB of reads per block before it, a launch about
+// 3 us: up to eight blocks (32,768 nodes) the first pass is left out (rebuild, apply
+// and advance over 1,300 nodes with lists, with the cursors cleared here too: 47.7
+// -> 44.4 us).
+constexpr int64_t kScanSelfBlocks = 8;
 __global__ void __launch_bounds__(kBlock) k_scan_apply(const int32_t *in, int64_t n, const int32_t *sums,
-                                                       int own_prefix, int32_t *out, int32_t *total_out) {
+                                                       int how, int32_t *out, int32_t *total_out, int32_t *zero) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int32_t v[kScanItems];
     scan_load(in, base, n, v);
@@ -864,15 +919,28 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(const int32_t *in, int64_
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) s += v[k];
     int32_t prefix, total;
-    if (own_prefix) {
-        int32_t p = 0;
-        for (int64_t j = threadIdx.x; j < (int64_t)blockIdx.x; j += kBlock) p += sums[j];
-        block_exclusive_scan(p, &prefix);
-    } else {
+    if (how == kScanTop) {
         prefix = sums[blockIdx.x];
+    } else {
+        int32_t p = 0;
+        if (how == kScanSelf) {
+            for (int64_t b = 0; b < (int64_t)blockIdx.x; ++b) {
+                int32_t w[kScanItems];
+                scan_load(in, b * kScanTile + (int64_t)threadIdx.x * kScanItems, n, w);
+#pragma unroll
+                for (int k = 0; k < kScanItems; ++k) p += w[k];
+            }
+        } else {
+            for (int64_t j = threadIdx.x; j < (int64_t)blockIdx.x; j += kBlock) p += sums[j];
+        }
+        block_exclusive_scan(p, &prefix);
     }
+    if (zero)
+        for (int64_t i = (int64_t)blockIdx.x * kScanTile + threadIdx.x;
+             i < min(n, ((int64_t)blockIdx.x + 1) * kScanTile); i += kBlock)
+            zero[i] = 0;
     int32_t run = prefix + block_exclusive_scan(s, &total);
-    if (own_prefix && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total_out = prefix + total;
+    if (how != kScanTop && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total_out = prefix + total;
     int32_t o[kScanItems];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -2260,10 +2328,10 @@ hipError_t launch_probe(const DevTables &t, bool count, bool mark, int32_t *pair
     if (t.tail_lists) return hipErrorInvalidValue;  // the groups' grid (launch_probe_groups)
     const RecGroups none{};
     if (count)
-        hipLaunchKernelGGL(k_probe<true>, grid, dim3(kBlock), 0, s, t, (int64_t)0, t.N, do_mark, pairs, none,
+        hipLaunchKernelGGL((k_probe<true, false>), grid, dim3(kBlock), 0, s, t, (int64_t)0, t.N, do_mark, pairs, none,
                            (int64_t)0);
     else
-        hipLaunchKernelGGL(k_probe<false>, grid, dim3(kBlock), 0, s, t, (int64_t)0, t.N, do_mark, pairs, none,
+        hipLaunchKernelGGL((k_probe<false, false>), grid, dim3(kBlock), 0, s, t, (int64_t)0, t.N, do_mark, pairs, none,
                            (int64_t)0);
     return hipGetLastError();
 }
@@ -2287,7 +2355,7 @@ hipError_t launch_probe_groups(const DevTables &t, const RecGroups &rg, int64_t 
     if (!t.tail_lists || t.table || !pairs || !groups_ok(t, rg) || k0 < 0 || k1 > rg.n || k0 >= k1)
         return hipErrorInvalidValue;
     const int64_t b0 = rg.blk0[k0], b1 = rg.blk0[k1];
-    hipLaunchKernelGGL(k_probe<true>, dim3((unsigned)(b1 - b0)), dim3(kBlock), 0, s, t, (int64_t)0, t.N, 0, pairs,
+    hipLaunchKernelGGL((k_probe<true, true>), dim3((unsigned)(b1 - b0)), dim3(kBlock), 0, s, t, (int64_t)0, t.N, 0, pairs,
                        rg, b0);
     return hipGetLastError();
 }
@@ -2296,7 +2364,7 @@ hipError_t launch_count_range(const DevTables &t, int64_t m0, int64_t m1, hipStr
     if (m1 <= m0) return hipSuccess;
     if (m0 < 0 || m1 > t.N || t.table || t.tail_lists) return hipErrorInvalidValue;
     const RecGroups none{};
-    hipLaunchKernelGGL(k_probe<true>, dim3((unsigned)mark_blocks(m1 - m0)), dim3(kBlock), 0, s, t, m0, m1, 0,
+    hipLaunchKernelGGL((k_probe<true, false>), dim3((unsigned)mark_blocks(m1 - m0)), dim3(kBlock), 0, s, t, m0, m1, 0,
                        (int32_t *)nullptr, none, (int64_t)0);
     return hipGetLastError();
 }
@@ -2339,7 +2407,7 @@ void suf_sizes(SufBuild &b) {
     // at most 3.2 entries per bucket of eight on average (fewer: equal markers are
     // one entry), so that one bucket in 200 overflows; the scratch set at most
     // half full
-    b.buckets = b.entries * 5 / 16 + 64;
+    b.buckets = std::min<int64_t>(b.entries * 5 / 16 + 64, INT32_MAX / kSufSlots);  // entry numbers are 31 bits
     b.set_slots = 64;
     while (b.set_slots < 2 * b.entries) b.set_slots <<= 1;
 }
@@ -2360,7 +2428,7 @@ int64_t probe_nodes_per_block() { return kBlock; }
 
 hipError_t launch_fill_records(const DevTables &t, const RecGroups &rg, hipStream_t s) {
     if (!groups_ok(t, rg)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_fill_records, dim3((unsigned)rg.blk0[rg.n]), dim3(kWave), 0, s, t, rg);
+    hipLaunchKernelGGL(k_fill_records, dim3((unsigned)rg.blk0[rg.n]), dim3(kFillThreads), 0, s, t, rg);
     return hipGetLastError();
 }
 
@@ -2388,13 +2456,15 @@ hipError_t launch_format(const DevTables &t, int32_t *pairs, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const DevTables &t, hipStream_t s) {
+hipError_t launch_scan(const DevTables &t, int32_t *zero, hipStream_t s) {
     const int64_t nb = grid_for(t.N, kScanTile);
-    const int own = nb <= kScanTile ? 1 : 0;  // the apply pass adds up the block sums itself
-    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kBlock), 0, s, t.count, t.N, t.scan_tmp);
-    if (!own) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, t.scan_tmp, nb, t.row_ptr + t.N);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kBlock), 0, s, t.count, t.N, t.scan_tmp, own,
-                       t.row_ptr, t.row_ptr + t.N);
+    const int how = nb <= kScanSelfBlocks ? kScanSelf : nb <= kScanTile ? kScanOwn : kScanTop;
+    if (how != kScanSelf)
+        hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kBlock), 0, s, t.count, t.N, t.scan_tmp);
+    if (how == kScanTop)
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, t.scan_tmp, nb, t.row_ptr + t.N);
+    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kBlock), 0, s, t.count, t.N, t.scan_tmp, how,
+                       t.row_ptr, t.row_ptr + t.N, zero);
     return hipGetLastError();
 }
 

@@ -191,6 +191,14 @@ struct Arena {
 
 // ------------------------------------------------------------- vocabulary --
 
+// Stream s waits for the vocabulary's uploads if they may still be running (a
+// wait puts a barrier between the stream's kernels).
+hipError_t wait_vocab(const tam_vocab *v, hipStream_t s) {
+    if (hipEventQuery(v->ready) == hipSuccess) return hipSuccess;
+    (void)hipGetLastError();
+    return hipStreamWaitEvent(s, v->ready, 0);
+}
+
 // The vocabulary's tables in a DevTables, with the sizes they imply.
 void set_vocab_tables(tam::DevTables &t, const tam_vocab *v) {
     t.tok_off = v->d_tok_off;
@@ -208,6 +216,7 @@ void set_vocab_tables(tam::DevTables &t, const tam_vocab *v) {
     t.len_present = v->d_len_present;
     t.slot_mask = (uint64_t)v->fps.size() - 1;
     t.suf_buckets = (uint32_t)v->suf.buckets;
+    t.suf_dups = v->dups ? 1 : 0;
     t.len_mask = v->len_mask;
     t.max_len = (int32_t)v->max_tok_len;
     t.V = v->V;
@@ -471,13 +480,12 @@ tam_status run_device_phase(tam_handle *h, unsigned phases, hipStream_t s, bool 
         h->mark_from_ev4 = true;
     }
     if (lists) {
-        TAM_HIP(tam::launch_scan(t, s));
-        if (h->rec_groups.n > 0) {  // the probe pass left a record of each listed hit
+        const bool recorded = h->rec_groups.n > 0;  // the probe pass left a record of each listed hit
+        TAM_HIP(tam::launch_scan(t, recorded ? nullptr : t.cursor, s));
+        if (recorded)
             TAM_HIP(tam::launch_fill_records(t, h->rec_groups, s));
-        } else {
-            TAM_HIP(tam::launch_fill_i32(t.cursor, t.N, 0, s));
+        else
             TAM_HIP(tam::launch_fill_lists(t, s));
-        }
         h->lists_built = true;
     }
     if (timing) {
@@ -587,6 +595,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
     int64_t next_blk = 0, next_off = 0, listed_total = 0;  // early_tail: the groups' blocks, offsets, records
     size_t o_suf = 0, o_count = 0, o_kid_cnt = 0, o_kid_parent = 0, o_kid_rank = 0, o_kid_total = 0, o_strs = 0, o_err = 0;
     tam::DevTables te{};  // the trie and vocabulary tables the early counts read
+    size_t upload_end = 0;  // the uploaded tables are [o_blob, upload_end) of the trie's allocation
     bool enqueued = false;  // device work that reads host tables or writes device memory
     double hook_ms = 0;     // time spent in the two hooks (allocation and enqueue)
     auto planned = [&](tam_handle *hh) -> tam_status {
@@ -603,27 +612,29 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         hh->own_alloc = alloc == nullptr;
         if (alloc) hh->alloc = *alloc;
         Arena ta;
+        // what is uploaded lies together, so that a small trie goes in one copy
         o_blob = ta.take<uint8_t>(hh->blob_bytes);
+        o_strs = ta.take<tam::StrRec>(hh->K_unique);
+        o_tail_rec = ta.take<tam::TailRec>(split ? hh->K_unique : 0);
+        o_sub_end = ta.take<int32_t>((hh->flags & TAM_FLAG_LAZY_ROWS) ? hh->N : 0);
+        // a group's blocks start a new block of nodes: at most one more block
+        // than the whole range per group
+        const int64_t gblocks = tam::mark_blocks(hh->N) + tam::kMaxRecGroups;
+        o_rec_off_t = ta.take<int32_t>(early_tail ? gblocks + tam::kMaxRecGroups : 0);  // blocks + 1 per group
+        upload_end = ta.used;
         o_node_at = ta.take<int32_t>(hh->blob_bytes);
         o_node_pos = ta.take<int32_t>(hh->N);
         o_depth = ta.take<int32_t>(hh->N);
         o_walk = ta.take<tam::Walk>(hh->N);
         o_kid = ta.take<tam::Kid>(hh->K_unique);
-        o_sub_end = ta.take<int32_t>((hh->flags & TAM_FLAG_LAZY_ROWS) ? hh->N : 0);
         o_tail_span = ta.take<int32_t>(split ? hh->N : 0);
         o_row_of = ta.take<int32_t>(split ? hh->N : 0);
         o_row_at = ta.take<int32_t>(split ? hh->blob_bytes : 0);
-        o_tail_rec = ta.take<tam::TailRec>(split ? hh->K_unique : 0);
         o_suf = ta.take<tam::NodeSuf>(early_count || early_tail ? hh->N : 0);
         o_count = ta.take<int32_t>(early_count || early_tail ? hh->N : 0);
-        // a group's blocks start a new block of nodes: at most one more block
-        // than the whole range per group
-        const int64_t gblocks = tam::mark_blocks(hh->N) + tam::kMaxRecGroups;
         o_pairs_t = ta.take<int32_t>(early_tail ? gblocks : 0);
-        o_rec_off_t = ta.take<int32_t>(early_tail ? gblocks + tam::kMaxRecGroups : 0);  // blocks + 1 per group
         o_rec_cnt_t = ta.take<int32_t>(early_tail ? gblocks : 0);
         if (early_tail) hh->rec_off.resize((size_t)(gblocks + tam::kMaxRecGroups));
-        o_strs = ta.take<tam::StrRec>(hh->K_unique);
         o_kid_cnt = ta.take<int32_t>(hh->N);  // scratch of the children's build
         o_kid_parent = ta.take<int32_t>(hh->K_unique);
         o_kid_rank = ta.take<int32_t>(hh->K_unique);
@@ -662,7 +673,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         if (early_count || early_tail) {
             te.node_suf = reinterpret_cast<tam::NodeSuf *>(trie_base + o_suf);
             te.count = reinterpret_cast<int32_t *>(trie_base + o_count);
-            hipError_t e = hipStreamWaitEvent(s, vocab->ready, 0);
+            hipError_t e = wait_vocab(vocab, s);
             const bool timing = (hh->flags & TAM_FLAG_TIMING) != 0;
             if (e == hipSuccess && timing) e = create_events(hh);
             if (e == hipSuccess && timing) e = hipEventRecord(hh->ev[0], s);
@@ -699,18 +710,50 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
     auto emitted = [&](tam_handle *hh, const tam::TrieRange &r) -> tam_status {
         const auto t1 = std::chrono::steady_clock::now();
         hipError_t e = hipSuccess;
-        auto up = [&](size_t off, const void *src, int64_t lo, int64_t hi, size_t elem) {
-            if (e == hipSuccess && hi > lo) {
-                e = hipMemcpyAsync(trie_base + off + (size_t)lo * elem, static_cast<const uint8_t *>(src) + (size_t)lo * elem,
-                                   (size_t)(hi - lo) * elem, hipMemcpyHostToDevice, s);
-                enqueued = true;
+        // tail lists: the group's record regions (sized on the host from its strings)
+        const bool regions = early_tail && r.n_hi > r.n_lo;
+        const int64_t per = tam::probe_nodes_per_block();
+        const int64_t blocks = (r.n_hi - r.n_lo + per - 1) / per;
+        int64_t total = 0;
+        if (regions) {
+            if (hh->rec_groups.n >= tam::kMaxRecGroups ||
+                next_blk + blocks > tam::mark_blocks(hh->N) + tam::kMaxRecGroups ||
+                next_off + blocks + 1 > (int64_t)hh->rec_off.size()) {
+                err = "listed-hit regions exceed the probe grid";
+                return TAM_E_STATE;
             }
+            total = tam::group_regions(hh, vocab, r.s_lo, r.s_hi, r.n_lo, per, blocks, hh->rec_off.data() + next_off);
+            if (listed_total + total >= INT32_MAX) {
+                err = "more than 2^31-1 valid (node, token) pairs are possible";
+                return TAM_E_TOOLARGE;
+            }
+        }
+        // A trie written in one go whose tables take at most 1 MiB is staged and
+        // goes in one copy instead of four or five (6 us of host time each); the
+        // staging lives as long as the handle, as every other copied table.
+        const bool staged = r.n_lo == 0 && r.n_hi == hh->N && upload_end - o_blob <= (size_t(1) << 20);
+        if (staged) hh->staging.resize(upload_end - o_blob);
+        auto up = [&](size_t off, const void *src, int64_t lo, int64_t hi, size_t elem) {
+            if (e != hipSuccess || hi <= lo) return;
+            const uint8_t *from = static_cast<const uint8_t *>(src) + (size_t)lo * elem;
+            const size_t at = off + (size_t)lo * elem, bytes = (size_t)(hi - lo) * elem;
+            if (staged) {
+                std::memcpy(hh->staging.data() + (at - o_blob), from, bytes);
+                return;
+            }
+            e = hipMemcpyAsync(trie_base + at, from, bytes, hipMemcpyHostToDevice, s);
+            enqueued = true;
         };
         up(o_blob, hh->blob.data(), r.b_lo, r.b_hi, 1);
         up(o_strs, hh->strs.data(), r.s_lo, r.s_hi, sizeof(tam::StrRec));
         if (hh->flags & TAM_FLAG_LAZY_ROWS) up(o_sub_end, hh->sub_end.data(), r.n_lo, r.n_hi, 4);
         if (split)  // the tail tables are laid out on the device from these
             up(o_tail_rec, hh->tail_rec.data(), r.s_lo, r.s_hi, sizeof(tam::TailRec));
+        if (regions) up(o_rec_off_t, hh->rec_off.data(), next_off, next_off + blocks + 1, 4);
+        if (staged) {
+            e = hipMemcpyAsync(trie_base + o_blob, hh->staging.data(), hh->staging.size(), hipMemcpyHostToDevice, s);
+            enqueued = true;
+        }
         // the group's position and tail tables (from its strings), then (lists)
         // its counts; after the last group the children
         const tam::StrRec *strs = reinterpret_cast<const tam::StrRec *>(trie_base + o_strs);
@@ -732,23 +775,9 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
             if (e == hipSuccess) e = tam::launch_count_range(te, r.n_lo, r.n_hi, s);
             if (e == hipSuccess && timing && r.n_hi == hh->N) e = hipEventRecord(hh->ev[2], s);
         }
-        if (early_tail && e == hipSuccess && r.n_hi > r.n_lo) {
-            // the group's record regions (sized on the host from its strings),
-            // their upload, the group's record buffer, then its probe pass
-            const int64_t per = tam::probe_nodes_per_block();
-            const int64_t blocks = (r.n_hi - r.n_lo + per - 1) / per;
+        if (regions && e == hipSuccess) {
+            // the group's record buffer, then its probe pass
             tam::RecGroups &rg = hh->rec_groups;
-            if (rg.n >= tam::kMaxRecGroups || next_blk + blocks > tam::mark_blocks(hh->N) + tam::kMaxRecGroups ||
-                next_off + blocks + 1 > (int64_t)hh->rec_off.size()) {
-                err = "listed-hit regions exceed the probe grid";
-                return TAM_E_STATE;
-            }
-            const int64_t total = tam::group_regions(hh, vocab, r.s_lo, r.s_hi, r.n_lo, per, blocks,
-                                                     hh->rec_off.data() + next_off);
-            if (listed_total + total >= INT32_MAX) {
-                err = "more than 2^31-1 valid (node, token) pairs are possible";
-                return TAM_E_TOOLARGE;
-            }
             const size_t rec_bytes = (size_t)(3 * std::max<int64_t>(total, 1)) * sizeof(int32_t);
             int32_t *rec = static_cast<int32_t *>(dev_alloc(hh, rec_bytes));
             if (!rec) {
@@ -756,7 +785,6 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
                 return TAM_E_NOMEM;
             }
             hh->device_bytes += (int64_t)rec_bytes;
-            up(o_rec_off_t, hh->rec_off.data(), next_off, next_off + blocks + 1, 4);
             const int k = rg.n++;
             rg.n_lo[k] = r.n_lo;
             rg.n_hi[k] = r.n_hi;
@@ -940,7 +968,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
         destroy_handle(h);
         return fail(TAM_E_STATE, "tail lists without their records");
     }
-    hipError_t e = hipStreamWaitEvent(s, vocab->ready, 0);
+    hipError_t e = early ? hipSuccess : wait_vocab(vocab, s);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->work_done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(h->work_done, s);
     if (e == hipSuccess && (h->flags & TAM_FLAG_TIMING)) e = create_events(h);
@@ -1063,7 +1091,7 @@ tam_status compile_format(const uint8_t *classes, int64_t L, tam_vocab *vocab, c
     h->d_err = reinterpret_cast<int32_t *>(base + o_err);
     h->h_err = tam::err_slot_take();
     t.err = h->d_err;
-    hipError_t e = hipStreamWaitEvent(s, vocab->ready, 0);
+    hipError_t e = wait_vocab(vocab, s);
     if (e == hipSuccess) e = tam::launch_fill_i32(h->d_err, 1, 0, s);
     if (e == hipSuccess) e = hipMemcpyAsync(base + o_cls, h->classes.data(), h->classes.size(),
                                             hipMemcpyHostToDevice, s);
@@ -1132,10 +1160,7 @@ tam_status tam_format_rows_noalloc(const uint8_t *classes, int64_t L, int termin
     TAM_HIP(hipGetLastError());
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the vocabulary's uploads, if they may still be running
-    if (hipEventQuery(vocab->ready) != hipSuccess) {
-        (void)hipGetLastError();
-        TAM_HIP(hipStreamWaitEvent(s, vocab->ready, 0));
-    }
+    TAM_HIP(wait_vocab(vocab, s));
     tam::DevTables t{};
     t.tok_off = vocab->d_tok_off;
     t.tok_blob = vocab->d_tok_blob;

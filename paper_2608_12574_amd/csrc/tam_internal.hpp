@@ -117,7 +117,8 @@ void suf_sizes(SufBuild &b);  // buckets and set_slots from entries
 hipError_t launch_suffix_table(const DevTables &t, const SufBuild &b, hipStream_t s);
 // the heads of V tokens
 hipError_t launch_tok_heads(const uint32_t *tok_off, const uint8_t *tok_blob, int64_t V, TokHead *head, hipStream_t s);
-hipError_t launch_scan(const DevTables &t, hipStream_t s);
+// count -> row_ptr (exclusive prefix sums, the total at N); zero (or null): N values cleared
+hipError_t launch_scan(const DevTables &t, int32_t *zero, hipStream_t s);
 hipError_t launch_zero(uint64_t *p, int64_t words, hipStream_t s);
 int64_t mark_blocks(int64_t N);
 hipError_t launch_fill_lists(const DevTables &t, hipStream_t s);
@@ -178,6 +179,7 @@ struct tam_vocab {
 
     int64_t V = 0, W = 0, max_tok_len = 0, device_bytes = 0;
     uint64_t len_mask = 0;
+    bool dups = false;  // some token string has several ids
     double host_ms = 0, upload_ms = 0;
 
     // host tables
@@ -238,6 +240,7 @@ struct tam_handle {
     // the compile uploaded, each with its own buffer of records
     tam::RecGroups rec_groups{};
     tam::hvec<int32_t> rec_off;  // host copy of the groups' region offsets (see DevTables::rec_off)
+    tam::hvec<uint8_t> staging;  // the uploaded tables of a small trie, in device layout
     // character-position masks (tam_compile_format): L positions, their classes
     int64_t fmt_L = -1;
     std::vector<uint8_t> classes;
