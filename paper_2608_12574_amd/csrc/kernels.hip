@@ -1313,13 +1313,14 @@ __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
 // List and tail rows.  Grid: x = groups of kBlock*U chunks of one row, y = batch
 // row.  Thread i of a block owns chunks c0 + u*kBlock + i, so every store
 // instruction covers 4 KiB per block contiguously.  A block's life is the
-// dependent loads in front of its stores (node id; row_of with the tail's hits,
-// or list bounds, then ids), 1.3 us at which the chip's waves with one 16-byte
-// store per thread just reach the memory's rate: one more dependent load in
-// front cost 10% of a step.  Two chunks per thread for tail compression took
-// 28.2 -> 25.1 us per decode step of 256 bf16 rows over V = 262,144 (fill of the
-// same bytes alone: 21.2), over a forest 30.2 -> 26.9; three 27.2, four 27.2 us.
-// Plain lists are at the memory's rate with one (25.5 against 26.6 us with two).
+// dependent loads in front of its stores (node id; row_of with the suffixes of
+// the nodes below; their ids; for lists the bounds, then the ids), so a thread
+// needs several 16-byte stores for the chip's waves to reach the memory's rate.
+// Tail rows of 256 bf16 logits rows over V = 262,144, with 1 / 2 / 3 chunks per
+// thread: calls one after another 32.1 / 29.8 / 24.3 us over a code list, 33.8 / 28.9 /
+// 26.4 over a forest; a decode step (apply and advance) 33.8 / 26.0 / 26.6 and 34.8 /
+// 27.0 / 27.8: three.  Plain lists are at the memory's rate with one (25.5 against
+// 26.6 us per step with two).
 // Write-mostly: a chunk without a valid token is written and not read; a fully
 // valid chunk is skipped; a mixed chunk is read and merged, and stored by the same
 // instruction as the empty ones, so that a 128-byte line holding both is written
@@ -2489,16 +2490,18 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
     return hipGetLastError();
 }
 
-// U chunks per thread; grid.y is limited to 65535 rows per launch.
+// U chunks per thread (see kApplyWide; tail rows three where dense rows take two,
+// plain lists one); grid.y is limited to 65535 rows per launch.
 template <typename T, int U, bool kAligned>
 static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, T *logits,
                                     int64_t row_stride, int64_t nchunks, hipStream_t s) {
+    constexpr int kTail = U > 1 ? 3 : 1;
     for (int64_t r0 = 0; r0 < B; r0 += 65535) {
         const dim3 grid(grid_for(nchunks, kBlock * U), (unsigned)std::min<int64_t>(B - r0, 65535));
         T *p = logits + r0 * row_stride;
         if (t.row_of)
-            hipLaunchKernelGGL((k_apply<T, kApplyTail, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
-                               row_stride);
+            hipLaunchKernelGGL((k_apply<T, kApplyTail, kTail, kAligned>), dim3(grid_for(nchunks, kBlock * kTail), grid.y),
+                               dim3(kBlock), 0, s, t, node_ids + r0, p, row_stride);
         else if (t.table)
             hipLaunchKernelGGL((k_apply_dense<T, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
                                row_stride);
