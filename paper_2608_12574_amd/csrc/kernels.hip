@@ -1322,8 +1322,8 @@ __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
 // 27.0 / 27.8: three.  Plain lists are at the memory's rate with one (25.5 against
 // 26.6 us per step with two).
 // Write-mostly: a chunk without a valid token is written and not read; a fully
-// valid chunk is skipped; a mixed chunk is read and merged, and stored by the same
-// instruction as the empty ones, so that a 128-byte line holding both is written
+// valid chunk is skipped; a mixed chunk of a tail or branching row is read and
+// merged, and stored by the same instruction as the empty ones, so that a 128-byte line holding both is written
 // whole (-inf stores into its invalid elements only, without the read, wrote such
 // lines in parts: 10,000 word strings from the root 32.0 -> 30.5 us per step, a
 // forest 26.9 -> 26.6).  The bits of the block's span come from the
@@ -1432,6 +1432,25 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
         if (whole_chunk<kAligned, E>(e0, V)) {
             u32x4 *p = reinterpret_cast<u32x4 *>(row + e0);
             const uint32_t w = neg_word<T>();
+            if (kMode == kApplyLists && bu != 0) {
+                // a plain list's row: -inf into the invalid elements only, no read
+                // (its chain of loads is the longest already: 23.0 against 27.2 us
+                // per call over a forest)
+                uint32_t *q = reinterpret_cast<uint32_t *>(p);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (sizeof(T) == 2) {
+                        const uint32_t two = (bu >> (2 * i)) & 3u;
+                        if (two == 0)
+                            q[i] = w;
+                        else if (two != 3u)
+                            row[e0 + 2 * i + (two == 1u ? 1 : 0)] = NegInf<T>::bits;
+                    } else if (!((bu >> i) & 1u)) {
+                        q[i] = w;
+                    }
+                }
+                continue;
+            }
             u32x4 o{w, w, w, w};
             if (bu != 0) o = merge_chunk<T>(*p, bu);
             __builtin_nontemporal_store(o, p);
