@@ -51,12 +51,16 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWave = 64;
-// Apply: two chunks per thread while that leaves this many blocks (8 per CU, all
-// that run at once); with fewer, one per thread spreads a small batch further.
-// bf16 rows over V = 262,144 with tail compression, two against one: 1 row 3.4
-// and 3.1 us, 8 rows 3.9 and 3.7, 16 rows 4.2 and 4.1, 32 rows (2,048 blocks) 5.35
-// and 5.44, 256 rows 20.0 and 23.3 us.
-constexpr int64_t kApplyWide = 2048;
+// Apply (dense and tail rows): two chunks per thread while that leaves this many
+// blocks (4 per CU); with fewer, one per thread spreads a small batch further.  us
+// per call in a graph, two against one.  Tail rows, bf16 over V = 262,144: 4 rows
+// (256 blocks) 3.53 and 3.39, 8 rows 3.77 and 3.73, 16 rows (1,024 blocks) 4.05
+// and 4.28, 32 rows 5.14 and 5.34, 64 rows 7.9 and 8.7, 256 rows 23.5 and 31.3;
+// fp32, 8 rows (1,024) 4.03 and 4.34; V = 32,000, 64 rows (512) 3.91 and 3.73, 128
+// rows (1,024) 4.53 and 4.58.  Dense rows, V = 262,144: 8 rows 3.32 and 3.37, 16
+// rows 3.63 and 3.69, 32 rows 5.22 and 5.11, 64 rows 8.05 and 7.93, 256 rows 23.7
+// and 30.2; V = 32,000, 64 rows 3.68 and 3.61, 128 rows 4.30 and 4.46.
+constexpr int64_t kApplyWide = 1024;
 // k_apply row sources: the valid lists, or with tail compression per row the
 // tail's hits or the branching node's dense row or list
 constexpr int kApplyLists = 1, kApplyTail = 2;
@@ -1316,11 +1320,14 @@ __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
 // dependent loads in front of its stores (node id; row_of with the suffixes of
 // the nodes below; their ids; for lists the bounds, then the ids), so a thread
 // needs several 16-byte stores for the chip's waves to reach the memory's rate.
-// Tail rows of 256 bf16 logits rows over V = 262,144, with 1 / 2 / 3 chunks per
-// thread: calls one after another 32.1 / 29.8 / 24.3 us over a code list, 33.8 / 28.9 /
-// 26.4 over a forest; a decode step (apply and advance) 33.8 / 26.0 / 26.6 and 34.8 /
-// 27.0 / 27.8: three.  Plain lists are at the memory's rate with one (25.5 against
-// 26.6 us per step with two).
+// Tail rows, 256 logits rows, with 1 / 2 / 3 chunks per thread, us per decode step
+// (apply and advance): bf16 over V = 262,144, a code list 34.6 / 26.8 / 27.1, a
+// forest 34.4 / 27.6 / 28.3; fp32 61.3 / 45.6 / 51.1; unaligned bf16 35.5 / 30.9 / 34.0;
+// calls one after another rank the same.  From the root of 10,000 word strings, where
+// most rows are branching ones with long chains of their own, three is the better
+// one (36.2 / 32.0 / 30.5); which rows a batch has is not known at the launch: two.
+// Plain lists are at the memory's rate with one (25.5 against 26.6 us per step with
+// two).
 // Write-mostly: a chunk without a valid token is written and not read; a fully
 // valid chunk is skipped; a mixed chunk of a tail or branching row is read and
 // merged, and stored by the same instruction as the empty ones, so that a 128-byte line holding both is written
@@ -1385,7 +1392,10 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
                 v = t.dup_next[v];
             }
         }
-        if (t.tail_long || t.tail_lists) {  // tokens longer than the window: the tail's list
+        // tokens longer than the window: the tail's list (without such tokens always
+        // empty; reading its bounds all the same is one more dependent load in front
+        // of the stores: anywhere in a forest 27.9 -> 26.7 us per step)
+        if ((t.tail_long || t.tail_lists) && t.max_len > kWin) {
             const int32_t e0 = t.row_ptr[n], e1 = t.row_ptr[n + 1];
             for (int32_t k0 = e0; k0 < e1; k0 += kWave) {
                 const uint32_t rel = k0 + lane < e1 ? (uint32_t)t.entries[k0 + lane] - lo : 0xffffffffu;
@@ -2509,18 +2519,17 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
     return hipGetLastError();
 }
 
-// U chunks per thread (see kApplyWide; tail rows three where dense rows take two,
-// plain lists one); grid.y is limited to 65535 rows per launch.
+// U chunks per thread (see kApplyWide; plain lists always one); grid.y is limited to
+// 65535 rows per launch.
 template <typename T, int U, bool kAligned>
 static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, T *logits,
                                     int64_t row_stride, int64_t nchunks, hipStream_t s) {
-    constexpr int kTail = U > 1 ? 3 : 1;
     for (int64_t r0 = 0; r0 < B; r0 += 65535) {
         const dim3 grid(grid_for(nchunks, kBlock * U), (unsigned)std::min<int64_t>(B - r0, 65535));
         T *p = logits + r0 * row_stride;
         if (t.row_of)
-            hipLaunchKernelGGL((k_apply<T, kApplyTail, kTail, kAligned>), dim3(grid_for(nchunks, kBlock * kTail), grid.y),
-                               dim3(kBlock), 0, s, t, node_ids + r0, p, row_stride);
+            hipLaunchKernelGGL((k_apply<T, kApplyTail, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
+                               row_stride);
         else if (t.table)
             hipLaunchKernelGGL((k_apply_dense<T, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
                                row_stride);
