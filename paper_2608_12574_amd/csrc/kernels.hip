@@ -1544,17 +1544,22 @@ __global__ void __launch_bounds__(kBlock) k_lay_init(int32_t *node_at, int64_t b
     if (i == 0) *err = *kid_total = 0;
 }
 
-// One wave per string record of [s0, s1); a record that does not fit the tables
-// is counted in *err.  One thread per string wrote each table with 64 separate
-// lines per store and walked its characters one after another, and the tables
-// took six kernels (positions and tail tables, first positions by an atomicMin):
-// 37 us for 500 strings of 60 bytes against 5.8 us, 61 us for 32,000 strings of
-// a forest against 31 us.
+// One wave per string record of [u0, s1) of the group that begins at s0; a record
+// that does not fit the tables is counted in *err.  One thread per string wrote
+// each table with 64 separate lines per store and walked its characters one after
+// another, and the tables took six kernels (positions and tail tables, first
+// positions by an atomicMin): 37 us for 500 strings of 60 bytes against 5.8 us, 61
+// us for 32,000 strings of a forest against 31 us.
+// A launch has fewer than 2^32 threads, so 2^26 waves, and a set may have more
+// strings: a launch takes kLayStrings of them.  (Waves striding over the strings
+// instead: 25 us more for 500 strings.)
+constexpr int64_t kLayStrings = 1 << 18;
+static_assert(kLayStrings * kWave < (int64_t(1) << 32), "threads of a launch");
 __global__ void __launch_bounds__(kBlock) k_lay(const StrRec *__restrict__ strs, const TailRec *__restrict__ trec,
-                                                int64_t s0, int64_t s1, int64_t blob_bytes, int64_t N, LayTables o,
-                                                int32_t *kid_cnt, int32_t *__restrict__ kid_parent,
+                                                int64_t s0, int64_t u0, int64_t s1, int64_t blob_bytes, int64_t N,
+                                                LayTables o, int32_t *kid_cnt, int32_t *__restrict__ kid_parent,
                                                 int32_t *__restrict__ kid_rank, int32_t *err) {
-    const int64_t u = s0 + ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
+    const int64_t u = u0 + ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     if (u >= s1) return;  // uniform over the wave
     int32_t par;
@@ -2412,9 +2417,14 @@ hipError_t launch_lay(const StrRec *strs, const TailRec *trec, int64_t s0, int64
                       hipStream_t s) {
     if (s1 <= s0) return hipSuccess;
     if ((trec != nullptr) != (o.row_of != nullptr)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_lay, dim3(grid_for(s1 - s0, kBlock / kWave)), dim3(kBlock), 0, s, strs, trec, s0, s1,
-                       blob_bytes, N, o, kid_cnt, kid_parent, kid_rank, err);
-    return hipGetLastError();
+    for (int64_t u0 = s0; u0 < s1; u0 += kLayStrings) {
+        const int64_t u1 = std::min(u0 + kLayStrings, s1);
+        hipLaunchKernelGGL(k_lay, dim3(grid_for(u1 - u0, kBlock / kWave)), dim3(kBlock), 0, s, strs, trec, s0, u0, u1,
+                           blob_bytes, N, o, kid_cnt, kid_parent, kid_rank, err);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_kids(const StrRec *strs, int64_t K, int64_t N, Walk *walk, Kid *kid, const int32_t *kid_cnt,

@@ -1123,6 +1123,24 @@ def test_suffix_search_lengths(P, lengths):
         full_check(P, strings, vocab, flags=flags)[0].close()
 
 
+@pytest.mark.parametrize("flags", ["table", "tail_lists"])
+def test_more_strings_than_layout_launch(P, flags):
+    """More strings in one set than a launch of the layout takes (262,144)."""
+    letters = [bytes([c]) for c in b"abcdefghijklmnopqrstuvwxyz"]
+    strings = [a + b + c + d for a in letters[:15] for b in letters for c in letters for d in letters][:(1 << 18) + 37]
+    vocab = [bytes([c]) for c in range(256)] + [b"", b"oa", b"abc", b'z"', b"aaaa", strings[-1] + b'"']
+    o = Oracle(strings, vocab)
+    h = P.compile(strings, vocab, flags=0 if flags == "table" else P.FLAG_TAIL_LISTS | P.FLAG_NO_TABLE)
+    assert h.num_nodes == o.N
+    rng = np.random.default_rng(3)
+    nodes = np.concatenate([[0, o.N - 1], rng.integers(-1, o.N, size=500), np.arange(o.N - 200, o.N)]).astype(np.int32)
+    assert np.array_equal(gpu_rows(h, nodes[nodes >= 0]), o.mask_rows(nodes[nodes >= 0]))
+    for t in list(range(97, 123)) + [0x22] + list(range(256, len(vocab))):
+        toks = np.full(nodes.size, t)
+        assert np.array_equal(gpu_advance(h, nodes, toks), o.advance(nodes, toks)), vocab[t]
+    h.close()
+
+
 def test_many_rows_grid_split(P):
     """More than 65,535 batch rows in one call (the launcher splits the grid)."""
     strings = [b"ab", b"b"]
