@@ -131,8 +131,9 @@ enum {
 };
 
 /* Device allocator.  alloc returns device memory aligned to at least 256 bytes
- * (or NULL); free releases it.  Both are called on the calling thread, from
- * tam_compile and tam_destroy only. */
+ * (or NULL); free releases it.  Both are called on the calling thread, from the
+ * compile, vocabulary and destroy calls only (a vocabulary's free also from a
+ * compile against it, see tam_vocab_create). */
 typedef struct {
     void *(*alloc)(size_t bytes, void *ctx);
     void (*free)(void *ptr, void *ctx);
@@ -237,7 +238,11 @@ tam_status tam_compile(const uint8_t *str_bytes, const int64_t *str_off, int64_t
  *   flags               TAM_FLAG_HOST_ONLY (no device copy, for host-only
  *                       compiles) or 0; other bits are ignored.
  *   alloc               NULL = hipMalloc / hipFree; it must stay valid until the
- *                       vocabulary is freed (after its last handle).
+ *                       vocabulary is freed (after its last handle).  Two blocks:
+ *                       the tables, and scratch of their build (about a fifth
+ *                       of them), which the first compile that finds the build
+ *                       finished gives back on its own thread, or the release of
+ *                       the vocabulary.
  * The vocabulary is reference counted: every handle compiled against it holds
  * a reference, and tam_vocab_destroy drops the caller's.  Errors: TAM_E_INVAL,
  * TAM_E_NOMEM, TAM_E_DEVICE, TAM_E_TOOLARGE (V or token bytes beyond 2^31-1, a

@@ -199,6 +199,17 @@ hipError_t wait_vocab(const tam_vocab *v, hipStream_t s) {
     return hipStreamWaitEvent(s, v->ready, 0);
 }
 
+// Gives the scratch of the vocabulary's build back once the build has finished
+// (20 MB at 262,144 tokens, read by nothing after it): one of the compiles that
+// find it done, on that compile's thread, or the release below.
+void settle_vocab(const tam_vocab *v) {
+    if (!v->scratch.load()) return;
+    if (hipEventQuery(v->ready) == hipSuccess)
+        free_with(v->own_alloc, v->alloc, v->scratch.exchange(nullptr));
+    else
+        (void)hipGetLastError();
+}
+
 // The vocabulary's tables in a DevTables, with the sizes they imply.
 void set_vocab_tables(tam::DevTables &t, const tam_vocab *v) {
     t.tok_off = v->d_tok_off;
@@ -230,6 +241,7 @@ void vocab_release(tam_vocab *v) {
         (void)hipEventSynchronize(v->ready);
         (void)hipEventDestroy(v->ready);
     }
+    free_with(v->own_alloc, v->alloc, v->scratch.exchange(nullptr));
     free_with(v->own_alloc, v->alloc, v->arena);
     delete v;
 }
@@ -288,20 +300,23 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     tam::SufBuild &sb = v->suf;
     sb.strings = (int64_t)v->pay.size();
     tam::suf_sizes(sb);
-    const size_t o_str_off = a.take<uint32_t>(sb.strings), o_str_mask = a.take<uint32_t>(sb.strings);
-    const size_t o_str_total = a.take<int32_t>(sb.strings);
-    const size_t o_set = a.take<uint64_t>(sb.set_slots), o_cnt = a.take<int32_t>(sb.buckets);
-    const size_t o_counter = a.take<int32_t>(1);
     const size_t o_suf_fps = a.take<uint32_t>(4 * sb.buckets);
     const size_t o_suf_pay = a.take<tam::SufPay>(tam::kSufSlots * sb.buckets);
     const size_t o_suf_short = a.take<tam::SufRef>(tam::kShortEntries);
     const size_t o_suf_ids = a.take<int32_t>(sb.ids);
+    Arena b;  // what only the suffix table's build reads
+    const size_t o_str_off = b.take<uint32_t>(sb.strings), o_str_mask = b.take<uint32_t>(sb.strings);
+    const size_t o_str_total = b.take<int32_t>(sb.strings);
+    const size_t o_set = b.take<uint64_t>(sb.set_slots), o_cnt = b.take<int32_t>(sb.buckets);
+    const size_t o_counter = b.take<int32_t>(1);
     uint8_t *base = static_cast<uint8_t *>(alloc_with(v->own_alloc, v->alloc, a.used));
-    if (!base) {
-        delete v;
-        return fail(TAM_E_NOMEM, "device allocation failed (" + std::to_string(a.used) + " bytes requested)");
-    }
+    uint8_t *scratch = base ? static_cast<uint8_t *>(alloc_with(v->own_alloc, v->alloc, b.used)) : nullptr;
     v->arena = base;
+    v->scratch = scratch;
+    if (!scratch) {
+        vocab_release(v);
+        return fail(TAM_E_NOMEM, "device allocation failed (" + std::to_string(a.used + b.used) + " bytes requested)");
+    }
     v->device_bytes = (int64_t)a.used;
     v->d_tok_off = reinterpret_cast<const uint32_t *>(base + o_off);
     v->d_tok_blob = base + o_blob;
@@ -312,12 +327,12 @@ tam_status vocab_create(const uint8_t *tok_bytes, const int64_t *tok_off, int64_
     v->d_short_hits = reinterpret_cast<const int32_t *>(base + o_short);
     v->d_dup_next = reinterpret_cast<const int32_t *>(base + o_dup);
     v->d_len_present = base + o_len;
-    sb.str_off = reinterpret_cast<uint32_t *>(base + o_str_off);
-    sb.str_mask = reinterpret_cast<uint32_t *>(base + o_str_mask);
-    sb.str_total = reinterpret_cast<int32_t *>(base + o_str_total);
-    sb.set = reinterpret_cast<uint64_t *>(base + o_set);
-    sb.cnt = reinterpret_cast<int32_t *>(base + o_cnt);
-    sb.counter = reinterpret_cast<int32_t *>(base + o_counter);
+    sb.str_off = reinterpret_cast<uint32_t *>(scratch + o_str_off);
+    sb.str_mask = reinterpret_cast<uint32_t *>(scratch + o_str_mask);
+    sb.str_total = reinterpret_cast<int32_t *>(scratch + o_str_total);
+    sb.set = reinterpret_cast<uint64_t *>(scratch + o_set);
+    sb.cnt = reinterpret_cast<int32_t *>(scratch + o_cnt);
+    sb.counter = reinterpret_cast<int32_t *>(scratch + o_counter);
     sb.fps = reinterpret_cast<uint32_t *>(base + o_suf_fps);
     sb.pay = reinterpret_cast<tam::SufPay *>(base + o_suf_pay);
     sb.shrt = reinterpret_cast<tam::SufRef *>(base + o_suf_short);
@@ -609,6 +624,7 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
             err = "the vocabulary lives on another device";
             return TAM_E_STATE;
         }
+        settle_vocab(vocab);
         hh->own_alloc = alloc == nullptr;
         if (alloc) hh->alloc = *alloc;
         Arena ta;
@@ -1060,6 +1076,7 @@ tam_status compile_format(const uint8_t *classes, int64_t L, tam_vocab *vocab, c
         destroy_handle(h);
         return fail(TAM_E_STATE, "the vocabulary lives on another device");
     }
+    settle_vocab(vocab);
     h->own_alloc = alloc == nullptr;
     if (alloc) h->alloc = *alloc;
     h->npairs = tam::format_blocks(h->Wp);

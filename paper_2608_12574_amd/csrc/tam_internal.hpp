@@ -194,8 +194,10 @@ struct tam_vocab {
     tam::hvec<int32_t> dup_next;
     std::vector<int64_t> dup_cum;  // [max_len+1] see build_vocab (list size bound)
 
-    // device copies (one arena)
+    // device copies (one arena), and what only the suffix table's build reads,
+    // given back once that has finished (then null)
     void *arena = nullptr;
+    mutable std::atomic<void *> scratch{nullptr};
     const uint32_t *d_tok_off = nullptr;
     const uint8_t *d_tok_blob = nullptr;
     const tam::TokHead *d_tok_head = nullptr;  // built on the device

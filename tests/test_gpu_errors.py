@@ -3,6 +3,7 @@ arguments on a real handle, and the device error count of a good build.
 
 These are the conditions a host can force; none makes a kernel fault.
 """
+import concurrent.futures as cf
 import ctypes
 
 import numpy as np
@@ -130,6 +131,50 @@ def test_allocator_failure_in_vocabulary_and_format(P):
     L.tam_vocab_destroy(voc)
     torch.cuda.synchronize()
     assert not good.live
+
+
+@pytest.mark.parametrize("fail_at", [0, 1])
+def test_every_allocation_of_a_vocabulary_failing(P, fail_at):
+    tb, to = P.tam.csr([b"1", b"-", b'"', b"12", b"abc"])
+    a = CountingAllocator(P, fail_at=fail_at)
+    voc = ctypes.c_void_p()
+    p = lambda x: ctypes.c_void_p(x.ctypes.data)  # noqa: E731
+    assert P.lib().tam_vocab_create(p(tb), p(to), 5, 0, ctypes.byref(a.struct), None, ctypes.byref(voc)) == -3
+    torch.cuda.synchronize()
+    assert not voc.value and not a.live
+
+
+@pytest.mark.parametrize("kind", ["set", "format", "threads"])
+def test_vocabulary_build_scratch_is_given_back(P, kind):
+    """The scratch of the suffix table's build is freed once, by a compile that
+    finds the build finished (here also by two threads that compile at once), and
+    the handles compiled then have the rows of one with a vocabulary of its own."""
+    w = W.config(1)
+    v = P.Vocab(w.vocab)
+    live = v._alloc.live
+    before = sum(t.numel() for t in live.values())
+    first = P.compile(w.strings, w.vocab, flags=P.FLAG_TAIL_LISTS)
+    torch.cuda.synchronize()
+    if kind == "format":
+        P.compile_format([b"0123456789"] * 3, v).close()
+        hs = []
+    elif kind == "set":
+        hs = [P.compile(w.strings, v, flags=f) for f in (0, P.FLAG_LAZY_ROWS)]
+    else:
+        with cf.ThreadPoolExecutor(2) as ex:
+            hs = list(ex.map(lambda f: P.compile(w.strings, v, flags=f), (0, P.FLAG_NO_TABLE)))
+    after = sum(t.numel() for t in live.values())
+    assert len(live) == 1 and after < before
+    torch.cuda.synchronize()
+    nodes = torch.arange(first.num_nodes, dtype=torch.int32, device="cuda")
+    rows = first.export_rows(nodes)
+    for h in hs + [P.compile(w.strings, v)]:
+        assert torch.equal(h.export_rows(nodes), rows)
+        h.close()
+    first.close()
+    v.close()
+    torch.cuda.synchronize()
+    assert not live
 
 
 def test_serving_argument_errors_on_a_device_handle(P):
