@@ -1411,11 +1411,19 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
             take_ids<E, U>(lane < e1 - e0 ? (uint32_t)t.entries[e0 + lane] - lo : 0xffffffffu, bits);
         } else {
             // long list: scatter through an LDS bitmap of the block's span
+            constexpr int kIds = 4;
             for (int i = threadIdx.x; i < kSpan / 32; i += kBlock) bm[i] = 0;
             __syncthreads();
-            for (int32_t k = e0 + (int32_t)threadIdx.x; k < e1; k += kBlock) {
-                const uint32_t v = (uint32_t)t.entries[k] - lo;
-                if (v < (uint32_t)kSpan) atomicOr(&bm[v >> 5], 1u << (v & 31));
+            // (four ids per thread loaded together: the roots of a forest 26.1 -> 25.4
+            // us per call with two chunks per thread, of 10,000 word strings 31.1 -> 30.0)
+            for (int32_t k0 = e0 + (int32_t)threadIdx.x; k0 < e1; k0 += kIds * kBlock) {
+                uint32_t v[kIds];
+#pragma unroll
+                for (int i = 0; i < kIds; ++i)
+                    v[i] = k0 + i * kBlock < e1 ? (uint32_t)t.entries[k0 + i * kBlock] - lo : 0xffffffffu;
+#pragma unroll
+                for (int i = 0; i < kIds; ++i)
+                    if (v[i] < (uint32_t)kSpan) atomicOr(&bm[v[i] >> 5], 1u << (v[i] & 31));
             }
             __syncthreads();
 #pragma unroll

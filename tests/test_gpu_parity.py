@@ -1100,6 +1100,29 @@ def test_apply_two_chunks_per_thread(P, flags, V):
         assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, off)
 
 
+@pytest.mark.parametrize("n", [62, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2049])
+def test_apply_list_lengths(P, n):
+    """Root lists of n entries, around a wave's lanes, a block's threads and four ids
+    per thread, the ids spread over several blocks' spans; one and two chunks per
+    thread."""
+    V = 12301
+    two = [bytes([a, b]) for a in range(64, 128) for b in range(64, 128)]
+    rng = np.random.default_rng(n)
+    vocab = [b"~~%d" % i for i in range(V)]
+    for i, t in zip(rng.permutation(V)[:n], two):
+        vocab[int(i)] = t
+    o = Oracle(two, vocab)
+    assert int(np.unpackbits(o.mask_rows(np.array([0])).view(np.uint8)).sum()) == n
+    for flags in (P.FLAG_NO_TABLE, P.FLAG_NO_TABLE | P.FLAG_TAIL_LISTS):
+        h = P.compile(two, vocab, flags=flags)
+        for B, dtype in ((3, "fp32"), (5, "bf16"), (700, "bf16")):
+            nodes = np.zeros(B, dtype=np.int32)
+            nodes[1] = o.N - 1
+            check_apply(P, h, o, nodes, dtype, seed=n)                           # unaligned rows
+            check_apply(P, h, o, nodes, dtype, cols=V, stride=12304, seed=n)     # aligned rows
+        h.close()
+
+
 @pytest.mark.parametrize("lengths", [[d] for d in range(1, 18)] + [[1, 16], [2, 9], [3, 13, 16], [8, 10, 12], [4, 5, 17, 30],
                                                                     list(range(1, 17)), list(range(1, 20))],
                          ids=lambda x: "-".join(map(str, x)) if len(x) < 6 else "1..%d" % x[-1])
