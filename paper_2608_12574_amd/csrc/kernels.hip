@@ -53,13 +53,13 @@ constexpr int kBlock = 256;
 constexpr int kWave = 64;
 // Apply (dense and tail rows): two chunks per thread while that leaves this many
 // blocks (4 per CU); with fewer, one per thread spreads a small batch further.  us
-// per call in a graph, two against one.  Tail rows, bf16 over V = 262,144: 4 rows
-// (256 blocks) 3.53 and 3.39, 8 rows 3.77 and 3.73, 16 rows (1,024 blocks) 4.05
-// and 4.28, 32 rows 5.14 and 5.34, 64 rows 7.9 and 8.7, 256 rows 23.5 and 31.3;
-// fp32, 8 rows (1,024) 4.03 and 4.34; V = 32,000, 64 rows (512) 3.91 and 3.73, 128
-// rows (1,024) 4.53 and 4.58.  Dense rows, V = 262,144: 8 rows 3.32 and 3.37, 16
-// rows 3.63 and 3.69, 32 rows 5.22 and 5.11, 64 rows 8.05 and 7.93, 256 rows 23.7
-// and 30.2; V = 32,000, 64 rows 3.68 and 3.61, 128 rows 4.30 and 4.46.
+// per call in a graph, new rows in every call, two against one.  Tail rows, bf16 over
+// V = 262,144: 8 rows (512 blocks) 3.10 and 3.00, 16 rows (1,024) 3.56 and 3.79, 32
+// rows 5.05 and 5.45, 64 rows 8.9 and 10.4, 256 rows 24.3 and 32.5; fp32, 8 rows
+// (1,024) 3.68 and 3.97; V = 32,000, 64 rows (512) 3.32 and 3.16, 128 rows (1,024)
+// 4.43 and 4.37.  Dense rows, V = 262,144: 8 rows 2.51 and 2.54, 32 rows 4.70 and
+// 5.00, 64 rows 7.7 and 8.5, 256 rows 30.1 and 37.3; V = 32,000, 64 rows 2.75 and
+// 2.75, 128 rows 3.43 and 3.63.
 constexpr int64_t kApplyWide = 1024;
 // k_apply row sources: the valid lists, or with tail compression per row the
 // tail's hits or the branching node's dense row or list
@@ -1321,11 +1321,13 @@ __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
 // the nodes below; their ids; for lists the bounds, then the ids), so a thread
 // needs several 16-byte stores for the chip's waves to reach the memory's rate.
 // Tail rows, 256 logits rows, with 1 / 2 / 3 chunks per thread, us per decode step
-// (apply and advance): bf16 over V = 262,144, a code list 34.6 / 26.8 / 27.1, a
-// forest 34.4 / 27.6 / 28.3; fp32 61.3 / 45.6 / 51.1; unaligned bf16 35.5 / 30.9 / 34.0;
-// calls one after another rank the same.  From the root of 10,000 word strings, where
-// most rows are branching ones with long chains of their own, three is the better
-// one (36.2 / 32.0 / 30.5); which rows a batch has is not known at the launch: two.
+// (apply and advance): bf16 over V = 262,144, anywhere in a code list 35.7 / 27.2 /
+// 27.3, a forest 33.2 / 26.3 / 28.2; fp32 60.2 / 44.7 / 51.3; unaligned bf16 35.2 / 27.8 /
+// 27.4.  Over 10,000 word strings, where most rows are branching ones with long chains
+// of their own, three is the better one (26.6 / 23.4 / 22.9); which rows a batch has is
+// not known at the launch: two.  These are rows that change with every call, as a
+// decode's do: with the same few rows again and again their tables stay in the caches,
+// and one call takes 23.1 us (fp32 45.3).
 // Plain lists are at the memory's rate with one (25.5 against 26.6 us per step with
 // two).
 // Write-mostly: a chunk without a valid token is written and not read; a fully
@@ -2537,13 +2539,30 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
     return hipGetLastError();
 }
 
+// Blocks per row of a dense or tail launch.  Consecutive blocks go to the eight XCDs
+// in turn, so with a multiple of eight blocks per row each part of every row falls to
+// the same XCD; while the rows' tables come from HBM, which a decode's new rows do in
+// every step, that is the slower order.  One block more, which finds no chunk, turns
+// the order by one XCD from row to row.  us per call of 256 rows, new ones in every
+// call, with 8 k and 8 k + 1 blocks: tail rows, bf16 over V = 262,144 29.8 and 24.3, fp32
+// 45.2 and 41.8, bf16 over V = 128,255 18.7 and 15.7, fp32 over V = 32,000 10.3 and 9.5;
+// dense rows 30.4 and 30.1, 64.4 and 64.5, 18.3 and 17.5, 8.8 and 8.4.  Below two rounds
+// of the 2,048 blocks that run at once the block more costs what it gives or more (tail
+// rows over V = 128,255, 64 rows 6.30 and 6.45; V = 32,000, 256 rows of 8 and 9 blocks 5.65
+// and 6.43).
+static unsigned row_blocks(int64_t nchunks, int per, int64_t rows) {
+    const unsigned gx = grid_for(nchunks, per);
+    return (gx & 7u) == 0 && gx >= 16 && (int64_t)gx * rows >= 4096 ? gx + 1 : gx;
+}
+
 // U chunks per thread (see kApplyWide; plain lists always one); grid.y is limited to
 // 65535 rows per launch.
 template <typename T, int U, bool kAligned>
 static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, T *logits,
                                     int64_t row_stride, int64_t nchunks, hipStream_t s) {
     for (int64_t r0 = 0; r0 < B; r0 += 65535) {
-        const dim3 grid(grid_for(nchunks, kBlock * U), (unsigned)std::min<int64_t>(B - r0, 65535));
+        const int64_t rows = std::min<int64_t>(B - r0, 65535);
+        const dim3 grid(row_blocks(nchunks, kBlock * U, rows), (unsigned)rows);
         T *p = logits + r0 * row_stride;
         if (t.row_of)
             hipLaunchKernelGGL((k_apply<T, kApplyTail, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,

@@ -1100,6 +1100,35 @@ def test_apply_two_chunks_per_thread(P, flags, V):
         assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, off)
 
 
+@pytest.mark.parametrize("flags", ["table", "tail", "tail_lists"])
+def test_apply_a_block_more_per_row(P, flags):
+    """Batches on both sides of the rule that adds a block without chunks to each row:
+    16 blocks per row of 8,192 chunks, 256 rows with the block more and 255 without;
+    the last chunks of the rows whole, cut and (rows off by one element) shifted."""
+    w = W.config(1)
+    vocab = w.vocab[:32768] + [b"~~%d" % i for i in range(65536 - len(w.vocab[:32768]))]
+    f = {"table": 0, "tail": P.FLAG_TAIL_LISTS, "tail_lists": P.FLAG_TAIL_LISTS | P.FLAG_NO_TABLE}[flags]
+    for dtype, V, off in (("fp32", 32768, 0), ("fp32", 32000, 0), ("fp32", 32763, 1), ("bf16", 65536, 0), ("bf16", 65529, 1)):
+        voc = vocab[-V:]  # the byte tokens, if cut off, at the end again
+        voc = voc[:V - 256] + w.vocab[:256]
+        o = Oracle(w.strings, voc)
+        h = P.compile(w.strings, voc, flags=f)
+        np_t = np.uint16 if dtype == "bf16" else np.uint32
+        per = 8 if dtype == "bf16" else 4
+        stride = V + (-V) % per if off == 0 else V
+        for B in (255, 256):
+            nodes = np.random.default_rng(B).integers(-1, o.N + 1, size=B).astype(np.int32)
+            nodes[:16] = 0
+            x = host_logits(1, off + B * stride + 8, dtype, seed=off)
+            dev = x.cuda()
+            h.apply_mask(torch.as_tensor(nodes, device="cuda"), dev[0, off:off + B * stride].view(B, stride)[:, :V])
+            exp = bits_of(x).view(np_t).copy()
+            inner = exp[0, off:off + B * stride].reshape(B, stride)
+            inner[:, :V] = o.apply(nodes, np.ascontiguousarray(inner[:, :V]), 1 if dtype == "bf16" else 0)
+            assert np.array_equal(bits_of(dev).view(np_t), exp), (dtype, V, B)
+        h.close()
+
+
 @pytest.mark.parametrize("n", [62, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2049])
 def test_apply_list_lengths(P, n):
     """Root lists of n entries, around a wave's lanes, a block's threads and four ids
