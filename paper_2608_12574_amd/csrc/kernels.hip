@@ -1399,8 +1399,10 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
         // of the stores: anywhere in a forest 27.9 -> 26.7 us per step)
         if ((t.tail_long || t.tail_lists) && t.max_len > kWin) {
             const int32_t e0 = t.row_ptr[n], e1 = t.row_ptr[n + 1];
-            for (int32_t k0 = e0; k0 < e1; k0 += kWave) {
-                const uint32_t rel = k0 + lane < e1 ? (uint32_t)t.entries[k0 + lane] - lo : 0xffffffffu;
+            const int32_t *ids = t.entries + e0;  // positions as below
+            const uint32_t cnt = (uint32_t)(e1 - e0);
+            for (uint32_t k0 = 0; k0 < cnt; k0 += kWave) {
+                const uint32_t rel = k0 + lane < cnt ? (uint32_t)ids[k0 + lane] - lo : 0xffffffffu;
                 take_ids<E, U>(rel, bits);
             }
         }
@@ -1418,11 +1420,15 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
             __syncthreads();
             // (four ids per thread loaded together: the roots of a forest 26.1 -> 25.4
             // us per call with two chunks per thread, of 10,000 word strings 31.1 -> 30.0)
-            for (int32_t k0 = e0 + (int32_t)threadIdx.x; k0 < e1; k0 += kIds * kBlock) {
+            // Positions are counted from the list's start and unsigned: e0 + 1,023 more
+            // than a position may exceed 2^31 - 1 at the end of the largest lists.
+            const int32_t *ids = t.entries + e0;
+            const uint32_t cnt = (uint32_t)(e1 - e0);
+            for (uint32_t k0 = threadIdx.x; k0 < cnt; k0 += kIds * kBlock) {
                 uint32_t v[kIds];
 #pragma unroll
                 for (int i = 0; i < kIds; ++i)
-                    v[i] = k0 + i * kBlock < e1 ? (uint32_t)t.entries[k0 + i * kBlock] - lo : 0xffffffffu;
+                    v[i] = k0 + i * kBlock < cnt ? (uint32_t)ids[k0 + i * kBlock] - lo : 0xffffffffu;
 #pragma unroll
                 for (int i = 0; i < kIds; ++i)
                     if (v[i] < (uint32_t)kSpan) atomicOr(&bm[v[i] >> 5], 1u << (v[i] & 31));
