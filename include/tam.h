@@ -346,14 +346,16 @@ typedef struct {
     const int32_t *parent;    /* [N] node_at[node_pos - 1]; -1 at roots and unplaced nodes */
     int64_t errors;           /* inconsistent string records or positions met (0 for the
                                  library's own build; on the device the same count makes later
-                                 calls return TAM_E_DEVICE) */
+                                 calls return TAM_E_DEVICE), and entries of the other tables
+                                 laid out that differ from the host build's */
 } tam_layout;
 
 /*
- * tam_layout_get -- the device's trie layout computed on the host: the same
- * functions the layout kernels run on the device (node_at and depth from one
- * record per string, first positions, parents), run over the same records, so
- * that the layout can be checked without a GPU.  Only for TAM_FLAG_HOST_ONLY
+ * tam_layout_get -- the device's trie layout computed on the host: the function
+ * that the layout kernel runs on the device (positions, depths, edge bytes, the
+ * strings' parents and with TAM_FLAG_TAIL_LISTS the tail tables, from one or two
+ * records per string), run over the same records with a wave's 64 lanes, so that
+ * the layout can be checked without a GPU.  Only for TAM_FLAG_HOST_ONLY
  * handles of string sets (else TAM_E_STATE); computed at the first call, kept
  * until tam_destroy.  Errors: TAM_E_INVAL (null argument), TAM_E_STATE,
  * TAM_E_NOMEM.

@@ -1127,10 +1127,13 @@ tam_status compile_format(const uint8_t *classes, int64_t L, tam_vocab *vocab, c
     return TAM_OK;
 }
 
-// The device's trie layout on the host (tam_layout_get): the layout kernels'
-// functions over the host's string records, in one pass each.
+// The device's trie layout on the host (tam_layout_get): the layout kernel's
+// function over the host's string records with a wave's lanes one after another, and
+// the tables it writes beside the positions (walk, each string's parent, and under
+// tail compression row_of, tail_span and row_at) held against the host build's.
 void layout_on_host(tam_handle *h) {
     const int64_t BB = h->blob_bytes, N = h->N;
+    constexpr int32_t kLanes = 64, kUnset = INT32_MIN;
     h->lay_node_at.assign((size_t)BB, 0);  // the outer pads stand for root 0, as on the device
     h->lay_depth.assign((size_t)N, -1);
     h->lay_node_pos.assign((size_t)N, -1);
@@ -1139,10 +1142,31 @@ void layout_on_host(tam_handle *h) {
     int32_t *node_pos = h->lay_node_pos.data(), *parent = h->lay_parent.data();
     int64_t errors = 0;
     const int64_t K = (int64_t)h->strs.size();
-    const tam::LayTables lt{node_at, depth, node_pos, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
-    int32_t par;
-    for (int64_t u = 0; u < K; ++u)
-        errors += tam::lay_string(h->strs.data(), nullptr, 0, u, BB, N, lt, 0, 1, &par);
+    const bool tails = h->tails;
+    const size_t tn = tails ? (size_t)N : 0;
+    std::vector<tam::Walk> walk((size_t)N, tam::Walk{kUnset, 0});
+    std::vector<int32_t> row_of(tn, kUnset), tail_span(tn, kUnset), row_at(tails ? (size_t)BB : 0, kUnset);
+    const tam::LayTables lt{node_at, depth, node_pos, walk.data(), h->blob.data(), (uint32_t)h->terminator,
+                            tails ? row_of.data() : nullptr, tails ? tail_span.data() : nullptr,
+                            tails ? row_at.data() : nullptr};
+    for (int64_t u = 0; u < K; ++u) {
+        const tam::StrRec &r = h->strs[(size_t)u];
+        for (int32_t lane = 0; lane < kLanes; ++lane) {
+            int32_t par = -1;
+            errors += tam::lay_string(h->strs.data(), tails ? h->tail_rec.data() : nullptr, 0, u, BB, N, lt, lane,
+                                      kLanes, &par);
+            // the set's first string starts its root's own path
+            errors += par != (r.first == r.root + 1 ? -1 : h->parent[(size_t)r.first]);
+        }
+    }
+    for (int64_t g = 0; g < N; ++g) {
+        const uint32_t byte = walk[(size_t)g].nb;
+        errors += walk[(size_t)g].off != 0;
+        errors += h->parent[(size_t)g] < 0 ? byte > 0xff || byte == (uint32_t)h->terminator : byte != h->edge[(size_t)g];
+        if (tails) errors += (row_of[(size_t)g] != h->row_of[(size_t)g]) + (tail_span[(size_t)g] != h->tail_span[(size_t)g]);
+    }
+    if (tails)
+        for (int64_t p = tam::kBlobPad; p < BB - tam::kBlobPad; ++p) errors += row_at[(size_t)p] != h->row_at[(size_t)p];
     for (int64_t g = 0; g < N; ++g) {
         if (depth[g] == 0) continue;
         bool bad = false;

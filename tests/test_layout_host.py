@@ -160,3 +160,25 @@ def test_layout_needs_host_only_set_handle(P):
     with pytest.raises(P.TamError) as e:
         h.layout()
     assert e.value.status == -6
+
+
+@pytest.mark.parametrize("tails", [False, True], ids=["trie", "tails"])
+@pytest.mark.parametrize("nsets", [1, 3])
+def test_layout_tables_beside_positions(P, tails, nsets):
+    """The tables that the layout writes beside the positions (walk, the strings'
+    parents and under tail compression row_of, tail_span and row_at) against the host
+    build's, with paths at the edges of a wave's 64 lanes: ``errors`` counts the
+    entries that differ."""
+    rng = np.random.default_rng(64)
+    for trial in range(40):
+        strings, offs = [], [0]
+        for _ in range(nsets):
+            base = [bytes(rng.integers(97, 99, size=int(n), dtype=np.uint8)) for n in rng.choice([0, 1, 62, 63, 64, 65, 127, 128, 129, 200], size=4)]
+            # strings that leave another one at its k-th byte
+            grown = [s[:int(k)] + bytes(rng.integers(97, 100, size=int(m), dtype=np.uint8))
+                     for s in base for k, m in zip(rng.integers(0, len(s) + 1, size=3), rng.choice([0, 1, 63, 64, 70], size=3))]
+            strings += base + grown
+            offs.append(len(strings))
+        h = P.compile(strings, [b"a"], sets=offs, flags=P.FLAG_HOST_ONLY | (P.FLAG_TAIL_LISTS if tails else 0))
+        assert h.layout()["errors"] == 0, trial
+        h.close()
