@@ -104,13 +104,13 @@ enum {
      * remaining suffix, at most one per length (per distinct token string):
      * the short valid lists of the Appendix's memory-vs-speed trade-off.  They
      * are not stored: the path below a tail has consecutive ids, so the token
-     * of length d starting below tail a is the suffix hit of node a+d, kept by
-     * the probe pass; tokens longer than 16 bytes go to per-node lists.
+     * of length d starting below tail a is the one of length d among the suffixes of
+     * node a+d, which the probe pass keeps; tokens longer than 16 bytes go to per-node lists.
      * Results are identical to the full table, which holds dense_rows rows
      * instead of N (c. 2.5% of the nodes of a set of 10,000 code-like
      * strings).  With TAM_FLAG_NO_TABLE there is no table at all: the
      * branching nodes keep sparse valid lists instead of dense rows (the
-     * tails still read theirs from the probe hits), so a forest of many
+     * tails still read theirs from the nodes below), so a forest of many
      * per-query sets lists only 1-2% of its nodes. */
     TAM_FLAG_TAIL_LISTS = 1u << 3,
     /* Rows built on demand (the lazy computation of the Appendix's memory
@@ -299,9 +299,9 @@ enum {
     TAM_PHASE_ZERO = 1u << 1,  /* zero fill of the dense table */
     TAM_PHASE_MARK = 1u << 2,  /* suffix probes setting the valid bits of the zeroed table */
     TAM_PHASE_TABLE = TAM_PHASE_ZERO | TAM_PHASE_MARK,
-    TAM_PHASE_COUNT = 1u << 3  /* (with lists) the probe pass that writes the hits and counts the
+    TAM_PHASE_COUNT = 1u << 3  /* (with lists) the probe pass that writes the nodes' suffixes and counts the
                                   lists, without the prefix sum and fill: the lists already built
-                                  stay as they are (the pass recomputes the same hits); for timing
+                                  stay as they are (the pass recomputes the same suffixes); for timing
                                   the probe pass alone */
 };
 
@@ -400,8 +400,8 @@ tam_status tam_advance(const tam_handle *h, const int32_t *node_ids, const int32
  * zero when node_ids[r] is dead or out of range.  The canonical row is this
  * interface's reading of the appendix's "GPU-Based Masking Considerations"
  * (one bitmask per trie node, a bit per vocabulary token), whatever the
- * handle keeps internally (dense rows, tails read back from the probe hits,
- * sparse lists, or rows built on demand).
+ * handle keeps internally (dense rows, tails read back from the suffixes of the
+ * nodes below, sparse lists, or rows built on demand).
  *   node_ids  device int32[n]; out  device, 8-byte aligned, written whole.
  * Errors: TAM_E_INVAL (null pointer with n > 0, n < 0, misaligned out),
  * TAM_E_STATE (host-only handle), TAM_E_DEVICE.
@@ -415,7 +415,7 @@ tam_status tam_export_rows(const tam_handle *h, const int32_t *node_ids, int64_t
  * the appendix tabulates by trie depth ("Valid set size distribution"), and
  * what a caller needs to choose between masking with the row and sampling
  * from a short valid list.  Counted on the device from the handle's own rows
- * (popcount of a dense row, a list's length, a tail's hits).
+ * (popcount of a dense row, a list's length, a tail's tokens).
  *   node_ids, out  device int32[n].
  * Errors: TAM_E_INVAL, TAM_E_STATE (host-only handle, or TAM_FLAG_LAZY_ROWS:
  * no row is kept for most nodes), TAM_E_DEVICE.

@@ -249,8 +249,9 @@ int host_threads(int64_t work_items) {
  * straight into the handle's tables.  Set j takes node ids
  * [roots[j], roots[j] + N_j) and its own range of the blob, which carries
  * kBlobPad zero bytes in front and behind so that 16-byte window loads around
- * any node never leave it.  Every node but a root has one parent edge, so
- * the child lists (built on the device) hold N - S entries.
+ * any node never leave it.  Each string but its set's first branches off one
+ * node, so the children that the device lists beside the strings' own paths are
+ * at most one per string.
  */
 tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int64_t *set_off,
                       int64_t S, int T, tam_handle *h, std::string *err,
@@ -319,7 +320,7 @@ tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int
     std::vector<PartBase> base((size_t)NP);
     std::vector<int64_t> root((size_t)S), set_blob((size_t)S), set_str((size_t)S);
     std::vector<int32_t> root_row((size_t)S);  // (tail split) row_of of each set root
-    int64_t N = 0, BB = kBlobPad, E = 0, rows = 0;
+    int64_t N = 0, BB = kBlobPad, rows = 0;
     h->K_unique = 0;
     for (int64_t j = 0; j < S; ++j) {
         root[(size_t)j] = N++;
@@ -352,7 +353,6 @@ tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int
             pb.str0 = h->K_unique;
             N += r.nodes - 1;
             BB += r.blob;
-            E += r.nodes - 1;  // every node but a root has one parent
             h->K_unique += (int64_t)r.str.size();
             if (N >= INT32_MAX || BB >= INT32_MAX || h->K_unique >= INT32_MAX) {
                 *err = "trie exceeds 2^31-1 nodes, strings or string bytes";
@@ -368,7 +368,6 @@ tam_status build_trie(const uint8_t *sb, const int64_t *so, int64_t K, const int
     h->N = N;
     h->S = S;
     h->blob_bytes = BB;
-    h->edges = E;
     if (planned) {  // sizes known, nothing emitted yet
         const tam_status st = planned(h);
         if (st != TAM_OK) return st;

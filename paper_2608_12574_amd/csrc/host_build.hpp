@@ -14,7 +14,7 @@ struct TrieRange {
     int64_t n_lo, n_hi, b_lo, b_hi, s_lo, s_hi;
 };
 
-// planned (optional) runs once the trie's sizes (N, S, blob bytes, edges) are
+// planned (optional) runs once the trie's sizes (N, S, blob bytes) are
 // set in h and before any node is written.  emitted (optional) runs after each
 // group of whole sets has been written (the trie's tables in those ranges,
 // tail compression's included, are then final).  A non-OK status of either

@@ -25,7 +25,7 @@
 //   k_advance-- B byte walks along the strings of the blob and over the
 //               children that leave them, one wave per row.
 //   k_export_dense, k_export_tail -- canonical rows out of the dense table and
-//               (tail compression) the probe's hits.
+//               (tail compression) the suffixes of the nodes below.
 // Rows built on demand (lazy computation with a bounded cache, Appendix):
 //   k_lazy_assign -- cache lookup and CLOCK replacement for a group of rows;
 //               each miss takes a zero spare row, its victim becomes a spare.
@@ -62,7 +62,8 @@ constexpr int kWave = 64;
 // 2.75, 128 rows 3.43 and 3.63.
 constexpr int64_t kApplyWide = 1024;
 // k_apply row sources: the valid lists, or with tail compression per row the
-// tail's hits or the branching node's dense row or list
+// tail's tokens (the suffixes of the nodes below it) or the branching node's dense
+// row or list
 constexpr int kApplyLists = 1, kApplyTail = 2;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -1337,7 +1338,7 @@ __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
 // lines in parts: 10,000 word strings from the root 32.0 -> 30.5 us per step, a
 // forest 26.9 -> 26.6).  The bits of the block's span come from the
 // node's valid list (a ballot over a short list, an LDS bitmap for a long one),
-// from the tail's hits, or (kApplyTail) from the dense row of a branching node.
+// from the suffixes of the nodes below a tail, or (kApplyTail) from the dense row of a branching node.
 // kAligned: every row's base is 16-byte aligned (no shift; computing it all the
 // same costs 1-2% of a forest's or a code list's decode step, as does unrolling
 // mask_partial).
@@ -1358,7 +1359,7 @@ __global__ void __launch_bounds__(kBlock) k_apply(DevTables t, const int32_t *__
     const int a = kAligned ? 0 : row_shift(row);
     const int64_t nchunks = (V + a + E - 1) / E;
     // the row's source (uniform over the block): its dense table row, its list,
-    // or (a tail with tail compression) the probe's hits along its path
+    // or (a tail with tail compression) the suffixes of the nodes on its path
     const int lane = threadIdx.x & (kWave - 1);
     // With tail compression most rows are tails: the suffixes of the nodes on the
     // path below n are loaded together with row_of[n] (lane d-1: those of node
@@ -1891,7 +1892,7 @@ __global__ void __launch_bounds__(kBlock) k_export_dense(DevTables t, const int3
 }
 
 // Tail rows (tail compression), one wave per requested row: the ids of the
-// tail's hits (as in k_apply) OR-ed into the zeroed output row.
+// tail's tokens (as in k_apply) OR-ed into the zeroed output row.
 __global__ void __launch_bounds__(kBlock) k_export_tail(DevTables t, const int32_t *nodes, int64_t nrows,
                                                         uint64_t *out) {
     const int64_t r = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
@@ -1920,7 +1921,7 @@ __global__ void __launch_bounds__(kBlock) k_export_tail(DevTables t, const int32
 }
 
 // |valid[n]| of the requested nodes, one wave per node: the popcount of its
-// dense row, the length of its list, or (a tail) its hits along the path plus
+// dense row, the length of its list, or (a tail) its tokens along the path plus
 // its long tokens' list; 0 for a dead node.  The same sources as k_apply.
 __global__ void __launch_bounds__(kBlock) k_row_counts(DevTables t, const int32_t *nodes, int64_t nrows,
                                                        int32_t *out) {

@@ -893,10 +893,10 @@ tam_status compile_with(const uint8_t *str_bytes, const int64_t *str_off, int64_
     const int64_t R = !want_table ? 0 : tails ? std::max<int64_t>(h->dense_rows, 1) : h->N;
 
     Arena a;
-    // the probe pass's tables (none when rows are built on demand; the hits and
-    // counts of early list counts are in the trie's allocation)
+    // the probe pass's tables (none when rows are built on demand; the node
+    // suffixes and counts of early list counts are in the trie's allocation)
     const int64_t NP = lazy ? 0 : h->N;
-    const bool early = early_count || early_tail;  // hits and counts are in the trie's allocation
+    const bool early = early_count || early_tail;  // both are in the trie's allocation
     const size_t o_suf_b = a.take<tam::NodeSuf>(early ? 0 : NP);
     const size_t o_count_b = a.take<int32_t>(early ? 0 : NP);
     const size_t o_row_ptr = a.take<int32_t>(NP + 1);

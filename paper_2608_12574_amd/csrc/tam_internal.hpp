@@ -127,9 +127,6 @@ int64_t probe_nodes_per_block();
 // tail compression without a table: the records of the listed hits (of
 // `blocks` probe blocks) into the lists
 hipError_t launch_fill_records(const DevTables &t, const RecGroups &rg, hipStream_t s);
-// the probe pass's counts over nodes [m0, m1) (lists, tail lists with their
-// records), with each block's valid pairs at pairs[blockIdx] (pairs may be null
-// without tail lists)
 // the probe pass (lists counted, records written) over groups [k0, k1) of the
 // groups' grid, into pairs[blocks of those groups]
 hipError_t launch_probe_groups(const DevTables &t, const RecGroups &rg, int64_t k0, int64_t k1, int32_t *pairs,
@@ -149,7 +146,7 @@ hipError_t launch_format_noalloc(const DevTables &t, const uint8_t *classes_host
                                  int64_t *pairs_out, hipStream_t s);
 hipError_t launch_export_dense(const DevTables &t, const int32_t *node_ids, int64_t n, uint64_t *out,
                                hipStream_t s);
-// OR the tails' tokens (from the probe hits) into exported rows (tail compression)
+// OR the tails' tokens (from their paths' suffixes) into exported rows (tail compression)
 hipError_t launch_export_tail(const DevTables &t, const int32_t *node_ids, int64_t n, uint64_t *out, hipStream_t s);
 int64_t scan_tmp_elems(int64_t N);
 // out[r] = |valid[node_ids[r]]| (0 for a dead node); not for rows built on demand
@@ -222,7 +219,7 @@ struct tam_handle {
     tam_allocator alloc{};
     tam_vocab *vocab = nullptr;  // one reference held by the handle
 
-    int64_t N = 0, S = 0, K_unique = 0, V = 0, W = 0, Wp = 0, edges = 0;
+    int64_t N = 0, S = 0, K_unique = 0, V = 0, W = 0, Wp = 0;
     int64_t blob_bytes = 0, entry_bound = 0, device_bytes = 0;
 
     // host trie tables
