@@ -544,12 +544,13 @@ __device__ __forceinline__ void wave_groups(int32_t x, uint64_t in, int lane, in
 // as that entry's list and mask (node_suf), 8 bytes per node; the tails of tail
 // compression read their tokens back from there.  Longer tokens are probed where
 // needed (long_hits).
-// Bound by the search's chain of five dependent loads and its VALU work (680
-// instructions per wave); L2 hit rate 0.83.  Probing every length on its own took
-// 14 bucket loads, 4.5 payloads and 64 bytes of hits per node, 101 M L2 requests
-// against 40 M over 5.4 M nodes, and every listed hit an atomic of its own on the few
-// ancestors that neighbouring nodes share: 645 us, now 222 us (370 with the
-// searches alone).
+// Bound by the search's chain of five dependent loads (the waves wait for 0.77 of
+// their time) and its VALU work (816 instructions per wave with records, 689 with
+// marks); L2 hit rate 0.87.  Probing every length on its own took 14 bucket loads,
+// 4.5 payloads and 64 bytes of hits per node, and every listed hit an atomic of its
+// own on the few ancestors that neighbouring nodes share: over a forest of 5.5 M
+// nodes 653 us and 1,482 MB read, now 207 us and 547 MB, 37 M L2 requests (370 us
+// with the searches alone).
 //   do_mark (a table): every hit whose ancestor has a dense row (row_at of its
 //     blob position; not a tail) is OR-ed into the zeroed table with a 64-bit
 //     atomic, and each block writes the number of valid (node, token) pairs its
