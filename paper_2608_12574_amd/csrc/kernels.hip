@@ -51,15 +51,17 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWave = 64;
-// Apply (dense and tail rows): two chunks per thread while that leaves this many
-// blocks (4 per CU); with fewer, one per thread spreads a small batch further.  us
-// per call in a graph, new rows in every call, two against one.  Tail rows, bf16 over
-// V = 262,144: 8 rows (512 blocks) 3.10 and 3.00, 16 rows (1,024) 3.56 and 3.79, 32
-// rows 5.05 and 5.45, 64 rows 8.9 and 10.4, 256 rows 24.3 and 32.5; fp32, 8 rows
-// (1,024) 3.68 and 3.97; V = 32,000, 64 rows (512) 3.32 and 3.16, 128 rows (1,024)
-// 4.43 and 4.37.  Dense rows, V = 262,144: 8 rows 2.51 and 2.54, 32 rows 4.70 and
-// 5.00, 64 rows 7.7 and 8.5, 256 rows 30.1 and 37.3; V = 32,000, 64 rows 2.75 and
-// 2.75, 128 rows 3.43 and 3.63.
+// Apply: two chunks per thread for dense rows, three for tail rows (see k_apply_dense
+// and k_apply), while that leaves this many blocks (4 per CU); with fewer, one per
+// thread spreads a small batch further.  us per call, one against two or three, new
+// rows in every call and, in brackets, after 1 GiB of other traffic.  Tail rows, bf16
+// over V = 262,144: 8 rows (344 blocks) 3.00 and 3.30 (5.2 and 5.4), 16 rows (688) 3.79
+// and 3.61 (5.7 and 6.3), 32 rows (1,376) 5.45 and 5.07 (8.6 and 7.2), 64 rows 10.4 and
+// 9.3 (14.8 and 11.7); V = 32,000, 128 rows (768) 4.37 and 4.20 (5.5 and 6.2), 256 rows
+// (1,536) 6.55 and 5.67 (9.6 and 7.8).  Dense rows, V = 262,144: 8 rows (512) 2.54 and
+// 2.51 (5.1 and 5.0), 32 rows (2,048) 5.00 and 4.70 (7.3 and 6.0), 64 rows 8.5 and 7.7
+// (12.0 and 9.4); V = 32,000, 128 rows (1,024) 3.63 and 3.43 (both 5.1).
+constexpr int kDenseChunks = 2, kTailChunks = 3;
 constexpr int64_t kApplyWide = 1024;
 // k_apply row sources: the valid lists, or with tail compression per row the
 // tail's tokens (the suffixes of the nodes below it) or the branching node's dense
@@ -1322,14 +1324,15 @@ __device__ __forceinline__ bool whole_chunk(int64_t e0, int64_t V) {
 // dependent loads in front of its stores (node id; row_of with the suffixes of
 // the nodes below; their ids; for lists the bounds, then the ids), so a thread
 // needs several 16-byte stores for the chip's waves to reach the memory's rate.
-// Tail rows, 256 logits rows, with 1 / 2 / 3 chunks per thread, us per decode step
-// (apply and advance): bf16 over V = 262,144, anywhere in a code list 35.7 / 27.2 /
-// 27.3, a forest 33.2 / 26.3 / 28.2; fp32 60.2 / 44.7 / 51.3; unaligned bf16 35.2 / 27.8 /
-// 27.4.  Over 10,000 word strings, where most rows are branching ones with long chains
-// of their own, three is the better one (26.6 / 23.4 / 22.9); which rows a batch has is
-// not known at the launch: two.  These are rows that change with every call, as a
-// decode's do: with the same few rows again and again their tables stay in the caches,
-// and one call takes 23.1 us (fp32 45.3).
+// Tail rows, 256 logits rows over V = 262,144, with 1 / 2 / 3 / 4 / 6 chunks per thread,
+// us per call.  After 1 GiB of other traffic, as a first pass or a decode behind a
+// model's forward meets them (every row's tables come from HBM, and each further
+// round of blocks waits for them again): anywhere in a code list 50.0 / 38.6 / 34.8 /
+// 31.8 / 28.8, over a forest's decode 51.9 / 40.6 / 36.2 / 34.3 / 31.2, fp32 93 / 68 / 61 / 56 /
+// 51.  One call after another on rows that the caches still hold, with two to six:
+// 24.6 / 24.9 / 27.6 / 26.4, 26.5 / 26.2 / 29.1 / 27.6, fp32 46.5 / 48.7 / 49.1 / 50.7.  New rows with
+// nothing in between: 32.5 / 24.3 / 24.3 / 28.3.  Three is near the best in the caches and 10%
+// better than two out of them.
 // Plain lists are at the memory's rate with one (25.5 against 26.6 us per step with
 // two).
 // Write-mostly: a chunk without a valid token is written and not read; a fully
@@ -2552,9 +2555,9 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
 // the same XCD; while the rows' tables come from HBM, which a decode's new rows do in
 // every step, that is the slower order.  One block more, which finds no chunk, turns
 // the order by one XCD from row to row.  us per call of 256 rows, new ones in every
-// call, with 8 k and 8 k + 1 blocks: tail rows, bf16 over V = 262,144 29.8 and 24.3, fp32
-// 45.2 and 41.8, bf16 over V = 128,255 18.7 and 15.7, fp32 over V = 32,000 10.3 and 9.5;
-// dense rows 30.4 and 30.1, 64.4 and 64.5, 18.3 and 17.5, 8.8 and 8.4.  Below two rounds
+// call, with 8 k and 8 k + 1 blocks of two chunks: tail rows, bf16 over V = 262,144 29.8
+// and 24.3, fp32 45.2 and 41.8, bf16 over V = 128,255 18.7 and 15.7, fp32 over V = 32,000
+// 10.3 and 9.5; dense rows 30.4 and 30.1, 64.4 and 64.5, 18.3 and 17.5, 8.8 and 8.4.  Below two rounds
 // of the 2,048 blocks that run at once the block more costs what it gives or more (tail
 // rows over V = 128,255, 64 rows 6.30 and 6.45; V = 32,000, 256 rows of 8 and 9 blocks 5.65
 // and 6.43).
@@ -2563,24 +2566,32 @@ static unsigned row_blocks(int64_t nchunks, int per, int64_t rows) {
     return (gx & 7u) == 0 && gx >= 16 && (int64_t)gx * rows >= 4096 ? gx + 1 : gx;
 }
 
-// U chunks per thread (see kApplyWide; plain lists always one); grid.y is limited to
-// 65535 rows per launch.
-template <typename T, int U, bool kAligned>
+// Two chunks per thread for dense rows and three for tail rows while that leaves
+// kApplyWide blocks, else one; plain lists always one.  grid.y is limited to 65535
+// rows per launch.
+template <typename T, bool kAligned>
 static hipError_t launch_apply_rows(const DevTables &t, const int32_t *node_ids, int64_t B, T *logits,
                                     int64_t row_stride, int64_t nchunks, hipStream_t s) {
+    const int per = kBlock * (t.row_of ? kTailChunks : kDenseChunks);
+    const bool wide = (t.row_of || t.table) && (int64_t)grid_for(nchunks, per) * B >= kApplyWide;
     for (int64_t r0 = 0; r0 < B; r0 += 65535) {
         const int64_t rows = std::min<int64_t>(B - r0, 65535);
-        const dim3 grid(row_blocks(nchunks, kBlock * U, rows), (unsigned)rows);
+        const dim3 grid(row_blocks(nchunks, wide ? per : kBlock, rows), (unsigned)rows);
+        const dim3 list_grid(grid_for(nchunks, kBlock), (unsigned)rows);
+        const int32_t *ids = node_ids + r0;
         T *p = logits + r0 * row_stride;
-        if (t.row_of)
-            hipLaunchKernelGGL((k_apply<T, kApplyTail, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
+        if (t.row_of && wide)
+            hipLaunchKernelGGL((k_apply<T, kApplyTail, kTailChunks, kAligned>), grid, dim3(kBlock), 0, s, t, ids, p,
+                               row_stride);
+        else if (t.row_of)
+            hipLaunchKernelGGL((k_apply<T, kApplyTail, 1, kAligned>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride);
+        else if (wide)
+            hipLaunchKernelGGL((k_apply_dense<T, kDenseChunks, kAligned>), grid, dim3(kBlock), 0, s, t, ids, p,
                                row_stride);
         else if (t.table)
-            hipLaunchKernelGGL((k_apply_dense<T, U, kAligned>), grid, dim3(kBlock), 0, s, t, node_ids + r0, p,
-                               row_stride);
+            hipLaunchKernelGGL((k_apply_dense<T, 1, kAligned>), grid, dim3(kBlock), 0, s, t, ids, p, row_stride);
         else
-            hipLaunchKernelGGL((k_apply<T, kApplyLists, 1, kAligned>),
-                               dim3(grid_for(nchunks, kBlock), grid.y), dim3(kBlock), 0, s, t, node_ids + r0, p,
+            hipLaunchKernelGGL((k_apply<T, kApplyLists, 1, kAligned>), list_grid, dim3(kBlock), 0, s, t, ids, p,
                                row_stride);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -2595,13 +2606,8 @@ static hipError_t launch_apply_typed(const DevTables &t, const int32_t *node_ids
     const bool aligned =
         (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && ((row_stride * (int64_t)sizeof(T)) & 15) == 0;
     const int64_t nchunks = (t.V + (aligned ? 0 : E - 1) + E - 1) / E;  // a shifted row may touch one more
-    // two chunks per thread while that leaves kApplyWide blocks
-    const bool wide = (int64_t)grid_for(nchunks, 2 * kBlock) * B >= kApplyWide;
-    if (aligned)
-        return wide ? launch_apply_rows<T, 2, true>(t, node_ids, B, logits, row_stride, nchunks, s)
-                    : launch_apply_rows<T, 1, true>(t, node_ids, B, logits, row_stride, nchunks, s);
-    return wide ? launch_apply_rows<T, 2, false>(t, node_ids, B, logits, row_stride, nchunks, s)
-                : launch_apply_rows<T, 1, false>(t, node_ids, B, logits, row_stride, nchunks, s);
+    return aligned ? launch_apply_rows<T, true>(t, node_ids, B, logits, row_stride, nchunks, s)
+                   : launch_apply_rows<T, false>(t, node_ids, B, logits, row_stride, nchunks, s);
 }
 
 hipError_t launch_apply(const DevTables &t, const int32_t *node_ids, int64_t B, void *logits, int dtype,

@@ -1103,12 +1103,15 @@ def test_apply_two_chunks_per_thread(P, flags, V):
 @pytest.mark.parametrize("flags", ["table", "tail", "tail_lists"])
 def test_apply_a_block_more_per_row(P, flags):
     """Batches on both sides of the rule that adds a block without chunks to each row:
-    16 blocks per row of 8,192 chunks, 256 rows with the block more and 255 without;
-    the last chunks of the rows whole, cut and (rows off by one element) shifted."""
+    16 blocks per row of two chunks per thread (three for tail rows), 256 rows with the
+    block more and 255 without; the last chunks of the rows whole, cut and (rows off
+    by one element) shifted."""
     w = W.config(1)
-    vocab = w.vocab[:32768] + [b"~~%d" % i for i in range(65536 - len(w.vocab[:32768]))]
+    vocab = w.vocab + [b"~~%d" % i for i in range(98304 - len(w.vocab))]
     f = {"table": 0, "tail": P.FLAG_TAIL_LISTS, "tail_lists": P.FLAG_TAIL_LISTS | P.FLAG_NO_TABLE}[flags]
-    for dtype, V, off in (("fp32", 32768, 0), ("fp32", 32000, 0), ("fp32", 32763, 1), ("bf16", 65536, 0), ("bf16", 65529, 1)):
+    n = 16 * 256 * (2 if flags == "table" else 3)  # chunks
+    for dtype, V, off in (("fp32", 4 * n, 0), ("fp32", 4 * n - 768, 0), ("fp32", 4 * n - 5, 1), ("bf16", 8 * n, 0),
+                          ("bf16", 8 * n - 7, 1)):
         voc = vocab[-V:]  # the byte tokens, if cut off, at the end again
         voc = voc[:V - 256] + w.vocab[:256]
         o = Oracle(w.strings, voc)
