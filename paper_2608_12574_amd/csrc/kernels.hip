@@ -2552,9 +2552,9 @@ hipError_t launch_rows(const DevTables &t, const int32_t *nodes, int64_t nrows, 
 
 // Blocks per row of a dense or tail launch.  Consecutive blocks go to the eight XCDs
 // in turn, so with a multiple of eight blocks per row each part of every row falls to
-// the same XCD; while the rows' tables come from HBM, which a decode's new rows do in
-// every step, that is the slower order.  One block more, which finds no chunk, turns
-// the order by one XCD from row to row.  us per call of 256 rows, new ones in every
+// the same XCD; with new rows in every call that was the slower order (not with rows
+// that the caches hold, nor behind 1 GiB of other traffic).  One block more, which
+// finds no chunk, turns the order by one XCD from row to row.  us per call of 256 rows, new ones in every
 // call, with 8 k and 8 k + 1 blocks of two chunks: tail rows, bf16 over V = 262,144 29.8
 // and 24.3, fp32 45.2 and 41.8, bf16 over V = 128,255 18.7 and 15.7, fp32 over V = 32,000
 // 10.3 and 9.5; dense rows 30.4 and 30.1, 64.4 and 64.5, 18.3 and 17.5, 8.8 and 8.4.  Below two rounds
